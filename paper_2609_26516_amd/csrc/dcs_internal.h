@@ -245,6 +245,37 @@ struct KsumArgs {
 };
 hipError_t launch_ksum(const KsumArgs& a, hipStream_t s);
 
+// A whole compression step of small branches in one launch, one workgroup per
+// branch (bra bonds up to CHAIN_MAX_D, operator bonds up to CHAIN_MAX_W).
+// tab (device): site offsets [n] and environment offsets [n + 1] inside a
+// slot's regions, then per branch {slot id, current MPS buffer, index of its
+// starting guess, 0, ket bond dims [n + 1], bra bond dims [n + 1], operator
+// bond dims [n + 1], operator offsets [n] from mpo}; offsets in units of 256
+// bytes.  f of branch b goes to nrm[b].
+constexpr int CHAIN_MAX_D = 32, CHAIN_MAX_W = 16;
+constexpr int CHAIN_LDS = 155 * 1024;   // of a workgroup, next to the static arrays
+struct ChainArgs {
+  char* slots;
+  long long slot_stride;
+  long long o_mps[2], o_env, o_x2;
+  const char* init;
+  long long mps_bytes;
+  const char* mpo;
+  const int* tab;
+  double* nrm;
+  int n, sweeps;
+  int lds_f, lds_scr, lds_x, lds_e, lds_ea, lds_k;   // set by launch_chain
+};
+// Largest of any branch and visit: bra bond, operator bond, operator elements
+// 4 wl wr, intermediate 2 D w K, environment D w K, ket site 2 K K.
+struct ChainDims {
+  int d_max, w_max, op_elems;
+  size_t x_elems, e_elems, k_elems;
+};
+inline constexpr int chain_rec_ints(int n) { return 4 + 3 * (n + 1) + n; }
+hipError_t launch_chain(int ct, const ChainArgs& a, int branches, const ChainDims& d,
+                        hipStream_t s);
+
 // Writes (1, 0), (0, 0) as two complex words at each listed address.
 hipError_t launch_fill_unit(int ct, void* const* ptrs_dev, int n, hipStream_t s);
 

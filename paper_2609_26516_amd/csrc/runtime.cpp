@@ -1384,6 +1384,30 @@ int dcs_chunk_destroy(dcs_chunk* ch) {
 
 namespace {
 
+// Host -> device copy through the state's pinned ring, ordered on stream s;
+// the source may be released as soon as this returns.
+int stage_h2d(dcs_state* st, hipStream_t s, void* dst, const void* src, size_t bytes) {
+  const int k = st->pin_next;
+  st->pin_next = (k + 1) % dcs_state::PIN_RING;
+  if (st->pin_done[k]) {
+    DCS_HIP(hipEventSynchronize(st->pin_done[k]));
+  } else {
+    DCS_HIP(hipEventCreateWithFlags(&st->pin_done[k], hipEventDisableTiming));
+  }
+  if (st->pin_bytes[k] < bytes) {
+    if (st->pin_buf[k]) DCS_HIP(hipHostFree(st->pin_buf[k]));
+    st->pin_buf[k] = nullptr;
+    st->pin_bytes[k] = 0;
+    const size_t want = std::max<size_t>(bytes, 4096);
+    DCS_HIP(hipHostMalloc(&st->pin_buf[k], want, hipHostMallocDefault));
+    st->pin_bytes[k] = want;
+  }
+  std::memcpy(st->pin_buf[k], src, bytes);
+  DCS_HIP(hipMemcpyAsync(dst, st->pin_buf[k], bytes, hipMemcpyHostToDevice, s));
+  DCS_HIP(hipEventRecord(st->pin_done[k], s));
+  return DCS_OK;
+}
+
 struct Group {
   std::vector<int> members;  // call indices
   int chi_cap = 0, cur = 0;
@@ -1392,6 +1416,117 @@ struct Group {
   const int* ids_dev = nullptr;
   bool warm = false;   // starting guess built from the ket (every ket bond <= the bra's)
 };
+
+// Largest bonds and intermediate of a compression step that one launch takes
+// (launch_chain), its algorithmic flops and operand bytes.
+struct ChainSize {
+  ChainDims d = {};
+  double flops = 0, bytes = 0;
+};
+
+// Whether one launch carries the whole step (launch_chain), one workgroup per
+// branch.  Up to bond dimension 16 that beats the chain of launches at every
+// batch (16 qubits, two sweeps, complex128: 0.71 against 1.57 ms for one branch,
+// 1.95 against 4.53 ms for 1024; operator bond 16: 1.20 against 2.59 ms).  Up to
+// 32 a visit is enough work to gain from several CUs, so it pays only while the
+// branches leave CUs idle and the operators are narrow (1.98 against 2.15 ms for
+// one branch, 2.06 against 2.67 ms for 64, but 4.30 against 3.91 ms for 300, and
+// 3.85 against 3.25 ms for one with operator bond 16).
+bool chain_takes(const dcs_state* st, const std::vector<Group>& groups, int branches) {
+  if (st->precision == DCS_BF16X3) return false;
+  int dmax = 0, wmax = 0;
+  for (const Group& g : groups) {
+    if (g.warm) return false;
+    for (int b = 0; b <= st->L.n; ++b) {
+      dmax = std::max(dmax, std::max(g.Db[b], g.Kb[b]));
+      wmax = std::max(wmax, g.w[b]);
+    }
+  }
+  if (dmax <= 16) return wmax <= CHAIN_MAX_W;
+  return dmax <= CHAIN_MAX_D && wmax <= 4 && branches <= 256;
+}
+
+// Uploads what launch_chain reads: the table of the branches, in group order,
+// and behind it the gate operators (one copy per distinct chunk).
+int chain_upload(dcs_state* st, const std::vector<Group>& groups, const int* ids,
+                 const dcs_chunk* const* chunks, int n, int sweeps, double* nrm, hipStream_t s,
+                 ChainArgs* ca, ChainSize* sz) {
+  *ca = {};
+  const Layout& L = st->L;
+  const int nq = L.n;
+  // the table first: its place is part of a captured launch, which may be
+  // replayed with other chunks of the same shapes
+  std::unordered_map<const dcs_chunk*, size_t> where;
+  auto op_bytes = [&](const dcs_chunk* c, int j) {
+    return align_up(c->site[j].size() * L.cs);
+  };
+  size_t bytes = align_up(((2 * (size_t)nq + 1) + (size_t)n * chain_rec_ints(nq)) * sizeof(int));
+  for (int i = 0; i < n; ++i)
+    if (where.emplace(chunks[i], bytes).second)
+      for (int j = 0; j < nq; ++j) bytes += op_bytes(chunks[i], j);
+  if (L.o_mpo + bytes > L.o_out) return fail(DCS_EINVAL, "internal: operator area too small");
+  st->host_stage.resize(std::max(st->host_stage.size(), bytes));
+  char* h = st->host_stage.data();
+  int* tab = reinterpret_cast<int*>(h);
+  for (int j = 0; j < nq; ++j) *tab++ = (int)(L.site_off[j] / ALIGN);
+  for (int b = 0; b <= nq; ++b) *tab++ = (int)(L.env_off[b] / ALIGN);
+  for (auto& w : where) {
+    size_t o = w.second;
+    for (int j = 0; j < nq; ++j) {
+      to_path_ct(L.ct, w.first->site[j].data(), w.first->site[j].size(), h + o);
+      o += op_bytes(w.first, j);
+    }
+  }
+  for (const Group& g : groups) {
+    const double k = (double)g.members.size();
+    for (int j = 0; j < nq; ++j) {
+      const double f = 2.0 * g.w[j] * g.w[j + 1];
+      const size_t xr = (size_t)2 * g.Db[j] * g.w[j + 1] * g.Kb[j + 1];
+      const size_t xl = (size_t)2 * g.Db[j + 1] * g.w[j] * g.Kb[j];
+      ChainDims& d = sz->d;
+      d.x_elems = std::max(d.x_elems, std::max(xr, xl));
+      d.d_max = std::max(d.d_max, std::max(g.Db[j], g.Db[j + 1]));
+      d.w_max = std::max(d.w_max, std::max(g.w[j], g.w[j + 1]));
+      d.op_elems = std::max(d.op_elems, 4 * g.w[j] * g.w[j + 1]);
+      d.e_elems = std::max(d.e_elems, (size_t)g.Db[j] * g.w[j] * g.Kb[j]);
+      d.k_elems = std::max(d.k_elems, (size_t)2 * g.Kb[j] * g.Kb[j + 1]);
+      // one environment and `sweeps` visits of the site
+      sz->flops += 8.0 * k * (sweeps + 1) *
+                   (2.0 * g.Db[j] * g.Kb[j + 1] * (g.w[j] * (double)g.Kb[j] + f) +
+                    2.0 * g.Db[j] * (double)g.Db[j + 1] * g.w[j + 1] * g.Kb[j + 1] * 2.0);
+      sz->bytes += k * L.cs * 2.0 * ((double)g.Kb[j] * g.Kb[j + 1] + (double)g.Db[j] * g.Db[j + 1]);
+    }
+    for (int i : g.members) {
+      *tab++ = ids[i];
+      *tab++ = g.cur;
+      *tab++ = st->init_index(g.chi_cap);
+      *tab++ = 0;
+      for (int v : g.Kb) *tab++ = v;
+      for (int v : g.Db) *tab++ = v;
+      for (int v : g.w) *tab++ = v;
+      size_t o = where[chunks[i]];
+      for (int j = 0; j < nq; ++j) {
+        *tab++ = (int)(o / ALIGN);
+        o += op_bytes(chunks[i], j);
+      }
+    }
+  }
+  DCS_TRY(stage_h2d(st, s, st->base + L.o_mpo, h, bytes));
+  ca->slots = st->base + L.o_slots;
+  ca->slot_stride = (long long)L.slot_stride;
+  ca->o_mps[0] = (long long)L.o_mps[0];
+  ca->o_mps[1] = (long long)L.o_mps[1];
+  ca->o_env = (long long)L.o_env;
+  ca->o_x2 = (long long)L.o_x2;
+  ca->init = st->base + L.o_init;
+  ca->mps_bytes = (long long)L.mps_bytes;
+  ca->mpo = st->base + L.o_mpo;
+  ca->tab = reinterpret_cast<const int*>(st->base + L.o_mpo);
+  ca->nrm = nrm;
+  ca->n = nq;
+  ca->sweeps = sweeps;
+  return DCS_OK;
+}
 
 }  // namespace
 
@@ -1453,9 +1588,14 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
       }
       groups[it->second].members.push_back(i);
     }
+    const bool chain = chain_takes(st, groups, n);
     // ids (group order) and gate operators (call-local, group order)
     std::vector<int> ids_host;
-    const size_t mpo_host_bytes = L.mpo_stride * (size_t)n;
+    double* nrm_dev = reinterpret_cast<double*>(st->base + L.o_out);
+    ChainArgs ca;
+    ChainSize csz;
+    if (chain) DCS_TRY(chain_upload(st, groups, ids, chunks, n, n_sweeps, nrm_dev, s, &ca, &csz));
+    const size_t mpo_host_bytes = chain ? 0 : L.mpo_stride * (size_t)n;
     st->host_stage.resize(std::max(st->host_stage.size(), mpo_host_bytes));
     char* mh = st->host_stage.data();
     for (auto& g : groups) {
@@ -1463,14 +1603,17 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
       for (int i : g.members) {
         const int ci = (int)ids_host.size();
         ids_host.push_back(ids[i]);
+        if (chain) continue;
         for (int j = 0; j < nq; ++j)
           to_path_ct(L.ct, chunks[i]->site[j].data(), chunks[i]->site[j].size(),
                      mh + L.mpo_stride * ci + L.mpo_site_off[j]);
       }
     }
     int* ids_dev = reinterpret_cast<int*>(st->base + L.o_ids);
-    DCS_HIP(hipMemcpyAsync(ids_dev, ids_host.data(), sizeof(int) * n, hipMemcpyHostToDevice, s));
-    DCS_HIP(hipMemcpyAsync(st->base + L.o_mpo, mh, mpo_host_bytes, hipMemcpyHostToDevice, s));
+    if (!chain) {
+      DCS_HIP(hipMemcpyAsync(ids_dev, ids_host.data(), sizeof(int) * n, hipMemcpyHostToDevice, s));
+      DCS_HIP(hipMemcpyAsync(st->base + L.o_mpo, mh, mpo_host_bytes, hipMemcpyHostToDevice, s));
+    }
     for (auto& g : groups) g.ids_dev = ids_dev + g.goff;
 
     const int ct = L.ct;
@@ -1478,7 +1621,6 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
     // products over the complex64 tensors
     const int acc = st->precision == DCS_BF16X3 ? ACC_BF16X3 : ct;
     const size_t cs = L.cs;
-    double* nrm_dev = reinterpret_cast<double*>(st->base + L.o_out);
     auto ket_site = [&](const Group& g, int j) { return slot_op(st, L.o_mps[g.cur], L.site_off[j]); };
     auto new_site = [&](const Group& g, int j) {
       return slot_op(st, L.o_mps[1 - g.cur], L.site_off[j]);
@@ -1689,6 +1831,11 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
         for (int j = nq - 2; j >= 0; --j) visits.push_back(j);
     }
     auto enqueue = [&]() -> int {
+      if (chain) {
+        Timed t(st->ctx, s, CLS_OTHER, csz.flops, csz.bytes);
+        DCS_HIP(launch_chain(ct, ca, n, csz.d, s));
+        return DCS_OK;
+      }
       DCS_TRY(warm_bra());
       // right environments of the starting guess
       for (int j = nq - 1; j >= 1; --j) {
@@ -1791,30 +1938,6 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
 // Measurement probability
 
 namespace {
-
-// Host -> device copy through the state's pinned ring, ordered on stream s;
-// the source may be released as soon as this returns.
-int stage_h2d(dcs_state* st, hipStream_t s, void* dst, const void* src, size_t bytes) {
-  const int k = st->pin_next;
-  st->pin_next = (k + 1) % dcs_state::PIN_RING;
-  if (st->pin_done[k]) {
-    DCS_HIP(hipEventSynchronize(st->pin_done[k]));
-  } else {
-    DCS_HIP(hipEventCreateWithFlags(&st->pin_done[k], hipEventDisableTiming));
-  }
-  if (st->pin_bytes[k] < bytes) {
-    if (st->pin_buf[k]) DCS_HIP(hipHostFree(st->pin_buf[k]));
-    st->pin_buf[k] = nullptr;
-    st->pin_bytes[k] = 0;
-    const size_t want = std::max<size_t>(bytes, 4096);
-    DCS_HIP(hipHostMalloc(&st->pin_buf[k], want, hipHostMallocDefault));
-    st->pin_bytes[k] = want;
-  }
-  std::memcpy(st->pin_buf[k], src, bytes);
-  DCS_HIP(hipMemcpyAsync(dst, st->pin_buf[k], bytes, hipMemcpyHostToDevice, s));
-  DCS_HIP(hipEventRecord(st->pin_done[k], s));
-  return DCS_OK;
-}
 
 // Enqueues the outcome norms (n_0, n_1) of branch ids[i] at qubits[i] into
 // the state's output area, FP64, at position pos[i] (branches grouped by
