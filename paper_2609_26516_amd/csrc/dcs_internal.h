@@ -196,6 +196,18 @@ struct CollapseItem {
 hipError_t launch_collapse(int ct, const CollapseItem* items_dev, int n_items, int max_elems,
                            hipStream_t s);
 
+// Device-to-device copies src -> dst of `bytes` each (multiples of 16, both
+// ends 16-byte aligned, no two overlapping), in one launch; max_bytes: the
+// longest.  At most 65535 segments per launch.
+struct CopySegment {
+  const char* src;
+  char* dst;
+  long long bytes, pad_;
+};
+constexpr int COPY_MAX_SEGMENTS = 65535;
+hipError_t launch_copy_segments(const CopySegment* segs_dev, int count, long long max_bytes,
+                                hipStream_t s);
+
 // Device-side sampling and collapse of site tensor A[dl][2][dr]: with
 // (n_0, n_1) = norms[2k], [2k + 1] and u = u[idx], outcome m = (u >= p_0),
 // switched to the other outcome if p_m <= eps; slice 1-m zeroed, slice m

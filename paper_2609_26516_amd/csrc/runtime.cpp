@@ -2204,18 +2204,42 @@ int dcs_collapse(dcs_state* st, int n, const int* src_ids, const int* qubits, co
     // copies first, so a source may also be collapsed in place
     std::vector<Slot> src_meta(n);
     for (int i = 0; i < n; ++i) src_meta[i] = st->slots[src_ids[i]];
+    std::vector<CopySegment> segs;
     for (int i = 0; i < n; ++i) {
       const int sid = src_ids[i], did = dst_ids[i];
       if (did == sid) continue;
       const Slot& sl = src_meta[i];
-      char* sb = st->slot_base(sid);
+      const char* sb = st->slot_base(sid);
       char* db = st->slot_base(did);
-      DCS_HIP(hipMemcpyAsync(db + L.o_mps[sl.cur], sb + L.o_mps[sl.cur], L.mps_bytes,
-                             hipMemcpyDeviceToDevice, s));
+      // the live part of every site; sites that meet (256-byte alignment
+      // aside) make one segment
+      size_t from = 0, to = 0;
+      for (int j = 0; j < L.n; ++j) {
+        const size_t end = L.site_off[j] + align_up((size_t)sl.dims[j] * 2 * sl.dims[j + 1] * L.cs);
+        if (L.site_off[j] != to) {
+          segs.push_back({sb + L.o_mps[sl.cur] + from, db + L.o_mps[sl.cur] + from,
+                          (long long)(to - from), 0});
+          from = L.site_off[j];
+        }
+        to = end;
+      }
+      segs.push_back({sb + L.o_mps[sl.cur] + from, db + L.o_mps[sl.cur] + from,
+                      (long long)(to - from), 0});
       if (sl.ecache_bond >= 0) {
         const size_t eb = (size_t)sl.dims[sl.ecache_bond] * sl.dims[sl.ecache_bond] * 16;
-        DCS_HIP(hipMemcpyAsync(db + L.o_e, sb + L.o_e, eb, hipMemcpyDeviceToDevice, s));
+        segs.push_back({sb + L.o_e, db + L.o_e, (long long)eb, 0});
       }
+    }
+    // (the item area holds n + 2 records of this size for every slot)
+    static_assert(sizeof(CopySegment) <= sizeof(CollapseItem), "segments fit the item area");
+    CopySegment* segs_dev = reinterpret_cast<CopySegment*>(st->base + L.o_items);
+    for (size_t k = 0; k < segs.size(); k += COPY_MAX_SEGMENTS) {
+      const int cnt = (int)std::min<size_t>(COPY_MAX_SEGMENTS, segs.size() - k);
+      long long longest = 0;
+      for (int i = 0; i < cnt; ++i) longest = std::max(longest, segs[k + i].bytes);
+      DCS_TRY(stage_h2d(st, s, segs_dev + k, segs.data() + k, sizeof(CopySegment) * cnt));
+      Timed t(st->ctx, s, CLS_OTHER, 0, 0);
+      DCS_HIP(launch_copy_segments(segs_dev + k, cnt, longest, s));
     }
     std::vector<CollapseItem> items(n);
     int max_elems = 0;
