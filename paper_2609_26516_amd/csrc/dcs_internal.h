@@ -288,6 +288,25 @@ inline constexpr int chain_rec_ints(int n) { return 4 + 3 * (n + 1) + n; }
 hipError_t launch_chain(int ct, const ChainArgs& a, int branches, const ChainDims& d,
                         hipStream_t s);
 
+// Outcome norms of small branches in one launch, one workgroup per branch
+// (bonds up to TRANSFER_MAX_D): branch b's (n_0, n_1) to out[2 b], out[2 b + 1],
+// the left transfer at its measured bond to its slot at o_e.  tab (device):
+// site offsets [n] (units of 256 bytes), then per branch {slot id, current MPS
+// buffer, qubit q, bond of the first left transfer (identity, or the cached one
+// if the next entry is not 0), cached, bond of the right identity, bond dims
+// [n + 1]}.
+constexpr int TRANSFER_MAX_D = 16;
+inline constexpr int transfer_rec_ints(int n) { return 6 + n + 1; }
+struct TransferArgs {
+  char* slots;
+  long long slot_stride;
+  long long o_mps[2], o_e;
+  const int* tab;
+  double* out;
+  int n;
+};
+hipError_t launch_transfer(int ct, const TransferArgs& a, int branches, hipStream_t s);
+
 // Writes (1, 0), (0, 0) as two complex words at each listed address.
 hipError_t launch_fill_unit(int ct, void* const* ptrs_dev, int n, hipStream_t s);
 

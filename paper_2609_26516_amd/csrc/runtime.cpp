@@ -1939,6 +1939,53 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
 
 namespace {
 
+// The same for small branches (launch_transfer): one launch instead of two per
+// site and transfer.
+int enqueue_norms_small(dcs_state* st, int n, const int* ids, const int* qubits, hipStream_t s) {
+  const Layout& L = st->L;
+  std::vector<int> tab(L.n + (size_t)n * transfer_rec_ints(L.n));
+  int* t = tab.data();
+  for (int j = 0; j < L.n; ++j) *t++ = (int)(L.site_off[j] / ALIGN);
+  double flops = 0, bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    Slot& sl = st->slots[ids[i]];
+    const int q = qubits[i];
+    int e_from = std::min(sl.lc_end, q), e_cached = 0;
+    if (sl.ecache_bond >= 0 && sl.ecache_bond <= q && sl.ecache_bond > e_from) {
+      e_from = sl.ecache_bond;
+      e_cached = 1;
+    }
+    const int g_from = std::max(sl.rc_start, q + 1);
+    *t++ = ids[i];
+    *t++ = sl.cur;
+    *t++ = q;
+    *t++ = e_from;
+    *t++ = e_cached;
+    *t++ = g_from;
+    for (int d : sl.dims) *t++ = d;
+    for (int j = e_from; j < g_from; ++j) {
+      const double dl = sl.dims[j], dr = sl.dims[j + 1];
+      flops += 8.0 * 4.0 * dl * dr * (j < q ? (dl + dr) / 2 : j > q ? (dl + dr) / 2 : 1.0);
+      bytes += 2.0 * dl * dr * L.cs;
+    }
+    if (e_cached || e_from < q) sl.ecache_bond = q;
+  }
+  int* dev = reinterpret_cast<int*>(st->base + L.o_items);   // 32 n + 64 bytes a slot
+  DCS_TRY(stage_h2d(st, s, dev, tab.data(), sizeof(int) * tab.size()));
+  TransferArgs a;
+  a.slots = st->base + L.o_slots;
+  a.slot_stride = (long long)L.slot_stride;
+  a.o_mps[0] = (long long)L.o_mps[0];
+  a.o_mps[1] = (long long)L.o_mps[1];
+  a.o_e = (long long)L.o_e;
+  a.tab = dev;
+  a.out = reinterpret_cast<double*>(st->base + L.o_out);
+  a.n = L.n;
+  Timed tm(st->ctx, s, CLS_MEAS, flops, bytes);
+  DCS_HIP(launch_transfer(L.ct, a, n, s));
+  return DCS_OK;
+}
+
 // Enqueues the outcome norms (n_0, n_1) of branch ids[i] at qubits[i] into
 // the state's output area, FP64, at position pos[i] (branches grouped by
 // shape).  Arguments are checked by the caller.
@@ -1946,6 +1993,17 @@ int enqueue_norms(dcs_state* st, int n, const int* ids, const int* qubits, hipSt
                   std::vector<int>& pos) {
   const Layout& L = st->L;
   const int ct = L.ct;
+  int d_max = 0;
+  for (int i = 0; i < n; ++i)
+    for (int d : st->slots[ids[i]].dims) d_max = std::max(d_max, d);
+  // One launch per call up to bond 16, where a site's products are a few tiles
+  // and the chain of launches is latency (see transfer_kernel for both sides);
+  // above, a branch's products are worth more than one workgroup.
+  if (d_max <= TRANSFER_MAX_D) {
+    pos.resize(n);
+    for (int i = 0; i < n; ++i) pos[i] = i;
+    return enqueue_norms_small(st, n, ids, qubits, s);
+  }
 
   struct MGroup {
     std::vector<int> members;

@@ -41,6 +41,16 @@ def _ops(rng, n, layers, far):
     return ops
 
 
+def _norms(mps, q):
+    e, g = np.eye(mps[0].shape[0]), np.eye(mps[-1].shape[2])
+    for a in mps[:q]:
+        e = np.einsum("ab,asc,bsd->cd", e, a.conj(), a, optimize=True)
+    for a in mps[:q:-1]:
+        g = np.einsum("asc,bsd,cd->ab", a.conj(), a, g, optimize=True)
+    return [float(np.einsum("ab,ac,bd,cd->", e, mps[q][:, m].conj(), mps[q][:, m], g,
+                            optimize=True).real) for m in (0, 1)]
+
+
 CASES = [
     # n, ket cap, bra cap, layers, far, sweeps
     (1, 1, 1, 0, False, 2), (2, 2, 2, 1, False, 3), (3, 1, 2, 2, False, 2), (5, 3, 3, 2, False, 1),
@@ -80,5 +90,42 @@ def test_one_launch_step(eng, n, kcap, bcap, layers, far, sweeps, kind, prec):
     if kind == "generic" and prec == "c128" and layers == 2 and kcap == bcap:
         for x, y in zip(got, ref):   # full rank: the tensors themselves, signs of the QR included
             assert np.max(np.abs(x - y)) <= 1e-9
+    capi.dcs_chunk_destroy(h)
+    st.close()
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("n,cap", [(1, 1), (2, 2), (5, 3), (8, 15), (9, 16), (9, 17)])
+def test_one_launch_measurement(eng, n, cap, prec):
+    """Outcome norms in one launch (bonds up to 16) and per site (above):
+    every qubit order, cached left transfer, states in no canonical form and
+    after a compression step.  The reference contracts the exported tensors in
+    FP64 over the same sites (transfers are the identity left of the last
+    left-canonical site and right of the first right-canonical one), so FP64
+    rounding of the contraction is all that separates the two sides."""
+    from paper_2609_26516_amd import capi
+    from paper_2609_26516_amd import engine as E
+    rng = np.random.default_rng([n, cap])
+    gauss = bra_init_gaussians(n, cap, 3)
+    st = E.State(eng, prec, n, 2, cap, 4, [cap], gaussians=lambda c: gauss)
+    ops = [((q, q + 1), C.haar_unitary(rng, 4)) for q in range(n - 1)] or [((0,), C.haar_unitary(rng, 2))]
+    h = capi.dcs_chunk_compile(eng.ctx, n, [q[0] for q, _ in ops],
+                               [q[1] if len(q) == 2 else -1 for q, _ in ops],
+                               np.concatenate([m.reshape(-1) for _, m in ops]))
+    for sweeps in (0, 1, 2):   # no canonical form, centre at the end, centre at site 0
+        for i in range(2):
+            capi.dcs_import_mps(st.h, i, cap, _ket(rng, n, cap, "generic"), eng.stream())
+        if sweeps:
+            st.compress([0, 1], [h, h], sweeps)
+        mps = [st.export(i) for i in range(2)]
+        for q in [n // 2, n - 1, 0, n // 2, *range(n)]:
+            other = n - 1 - q
+            got = st.measure([0, 1], [q, other])
+            for g, m, k in zip(got, mps, (q, other)):
+                c = None if sweeps == 0 else (n - 1 if sweeps == 1 else 0)   # orthogonality centre
+                lo = min(0 if c is None else c, k)
+                hi = max(n if c is None else c + 1, k + 1)
+                n0, n1 = _norms(m[lo:hi], k - lo)
+                assert abs(g - n0 / (n0 + n1)) <= 1e-12
     capi.dcs_chunk_destroy(h)
     st.close()
