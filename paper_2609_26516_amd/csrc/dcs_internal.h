@@ -152,6 +152,10 @@ int qr_spread_max_items();
 // block of each Q) from the explicit V (m x n) and the T factors after it at
 // each item's workspace.
 hipError_t launch_qr_qblocks(int ct_in, int ct_out, const QrArgs& args, int m_max, hipStream_t s);
+// Small and medium matrices (modes 0 and 1, n <= m <= QR_MID_M, n <= QR_MID_N)
+// in one launch, one workgroup of four waves per matrix; no workspace.
+constexpr int QR_MID_M = 128, QR_MID_N = 64;
+hipError_t launch_qr_mid(int ct_in, int ct_out, const QrArgs& args, hipStream_t s);
 int qr_large_max_rows();
 size_t qr_large_ws_elems(int m, int n);
 

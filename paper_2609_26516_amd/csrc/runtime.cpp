@@ -588,11 +588,13 @@ int run_mpo(dcs_ctx* ctx, int ct, int dir, const std::vector<MpoJob>& jobs, hipS
 using QrJob = rt::QrJob;
 
 // Path of a QR job: 0 blocked single-workgroup kernel, left-looking form
-// (m <= 512 or mode 2), 3 the spread path for the same matrices when `spread`
+// (m <= 512 or mode 2), 4 the one-launch form for small and medium matrices
+// when `mid`, 3 the spread path for the same matrices when `spread`
 // (see run_qr), 1 multi-kernel large-matrix path, 2 unblocked kernel (beyond
 // both).
-int qr_path(const QrJob& j, bool spread) {
+int qr_path(const QrJob& j, bool spread, bool mid) {
   if (j.mode == 2) return 0;
+  if (mid && j.m <= QR_MID_M && j.n <= QR_MID_N && j.m >= j.n) return 4;
   if (j.m <= qr_blocked_max_rows()) return spread && j.m >= j.n ? 3 : 0;
   return j.m <= qr_large_max_rows() ? 1 : 2;
 }
@@ -615,10 +617,18 @@ int run_qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& all, h
       n_big = std::max(n_big, j.n);
     }
   const bool spread = items <= qr_spread_max_items() && m_big > 128 && n_big >= 64;
-  for (int path : {0, 3, 1, 2}) {
+  // Matrices of up to 128 x 64 in one launch instead of a factorisation and a
+  // Q launch (or one launch of the blocked kernel from 161 matrices on): a step
+  // of 14 qubits at bond 45 takes 2.05 against 3.26 ms for 256 branches and 3.41
+  // against 4.31 ms for 512, at bond 64 1.82 against 2.41 ms for one and 4.26
+  // against 5.22 ms for 512.  Its larger matrices fill a CU's LDS, so many of
+  // them are left to the blocked kernel, which runs four to a CU (1024 of 128 x
+  // 64: 0.24 against 0.59 ms; of 90 x 45 the one launch is still ahead).
+  const bool mid = !spread && (items <= 512 || m_big <= 96);
+  for (int path : {0, 4, 3, 1, 2}) {
     std::vector<QrJob> jobs;
     for (const QrJob& j : all)
-      if (j.batch > 0 && qr_path(j, spread) == path) jobs.push_back(j);
+      if (j.batch > 0 && qr_path(j, spread, mid) == path) jobs.push_back(j);
     size_t i = 0;
     while (i < jobs.size()) {
       QrArgs args;
@@ -657,6 +667,8 @@ int run_qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& all, h
         // in separate launches so the Q blocks spread over the chip
         DCS_HIP(launch_qr_left(ct_in, ct_out, args, std::max(m_max, 1),
                                args.total_blocks <= qr_split_max_items(), s));
+      } else if (path == 4) {
+        DCS_HIP(launch_qr_mid(ct_in, ct_out, args, s));
       } else if (path == 3) {
         DCS_HIP(launch_qr_spread(ct_in, ct_out, args, s));
       } else if (path == 1) {

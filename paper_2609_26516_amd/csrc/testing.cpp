@@ -292,7 +292,11 @@ int dcs_test_qr(int ct_in, int ct_out, int m, int n, int mode, int use_lds, cons
     args.ngroups = 1;
     args.total_blocks = 1;
     const size_t lds = mn * 16;
-    if (use_lds == 7) {   // spread variant (small batches)
+    if (use_lds == 8) {   // one launch for small and medium matrices
+      if (mode == 2 || m > QR_MID_M || n > QR_MID_N || m < n)
+        return testing_fail(DCS_EINVAL, "the one-launch QR takes modes 0/1, n <= m <= 128, n <= 64");
+      T_HIP(launch_qr_mid(ct_in, ct_out, args, s));
+    } else if (use_lds == 7) {   // spread variant (small batches)
       if (mode == 2 || m > qr_spread_max_rows() || m < n)
         return testing_fail(DCS_EINVAL, "the spread QR takes modes 0/1 and n <= m <= 512");
       T_HIP(launch_qr_spread(ct_in, ct_out, args, s));
