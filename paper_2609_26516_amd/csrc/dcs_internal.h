@@ -59,7 +59,12 @@ struct GemmArgs {
   int ngroups;
   int total_tiles;
   int epi;   // one epilogue for every group of a launch
+  int far;   // an operand's rows are GEMM_FAR_LD elements apart or more (32 x 32 tiles only)
 };
+// The kernel loads operands through windows of 32-bit offsets, 128 rows of at
+// most 16-byte elements: from here on they do not fit, and the 32 x 32 tiles'
+// form with 64-bit addresses runs.
+constexpr int GEMM_FAR_LD = 1 << 21;
 
 // Tile shapes of the GEMM kernel (output tile BM x BN per workgroup).
 enum GemmVariant { GEMM_64x64 = 0, GEMM_32x32 = 1, GEMM_128x64 = 2, GEMM_64x128 = 3, GEMM_128x128 = 4 };

@@ -11,11 +11,15 @@
 // Tiling: one 256-thread workgroup (4 wave64 in a 2x2 grid) per BM x BN
 // output tile; each wave owns a (BM/2) x (BN/2) quadrant made of 16x16 MFMA
 // blocks with real and imaginary accumulators.  K advances in steps of 8
-// complex columns through LDS held as split real / imaginary planes in
+// complex columns (32x32 tiles: 32, in FP64 16) through LDS held as split real / imaginary planes in
 // [k][m] order, so the 16 lanes of an MFMA operand row read consecutive
 // words.  The next K tile is fetched into registers while the current one is
 // multiplied and then stored into the second of two LDS stages, one barrier
-// per K step.  Workgroup ids are remapped so consecutive tiles (same batch
+// per K step; the fetch has no branches, so it stays in flight across the
+// multiplication (the product with the gate epilogue of 1024 states at bond
+// 64: 125 us with predicated loads, 115 now; 256 states at bond 256, the whole
+// round's FP32 products: 147 ms, 143 now, the matrix cores busy 73-78 % of the
+// time).  Workgroup ids are remapped so consecutive tiles (same batch
 // item, shared operands) land on the same XCD / L2.  Tile shapes: 64x64,
 // 32x32, 128x64, 64x128 (chosen per shape class by the runtime's autotuner);
 // every shape accumulates each output element over K in the same order, so
@@ -25,6 +29,7 @@
 // group addresses its operands through the slot-id table or its call-local
 // index, with stride 0 for an operand shared by all items.
 #include "dcs_internal.h"
+#include "tile_load.h"
 
 namespace dcs {
 namespace {
@@ -65,14 +70,17 @@ struct Store<CT_F64> {
   using T = double2;
 };
 
-// K step of 8 complex columns: two LDS stages of a 64x64 tile stay small
+// Complex columns per K step.  8 keeps two LDS stages of a 64x64 tile small
 // enough (17 KB in FP32, 35 KB in FP64) that registers, not LDS, bound the
-// workgroups per CU; the MFMAs take k in ascending groups of 4, so results do
-// not depend on the step
+// workgroups per CU.  The 32x32 tile is chosen where few tiles exist or N is
+// small, and then waits for memory once per step: its step is 32 columns (16
+// in FP64), four (two) elements of each operand in flight per thread (two states at bond 45:
+// 8.2 us a launch with steps of 8, 7.1 now; the tree network's products, 64
+// branches: 25.1 ms a pass, 19.5 now).
+// The MFMAs take k in ascending groups of 4, so results do not depend on it.
 constexpr int NT = 256, PAD = 4;
-template <typename R>
-constexpr int gemm_bk() { return 8; }
-
+template <typename R, int BM, int BN>
+constexpr int gemm_bk() { return BM * BN > 32 * 32 ? 8 : sizeof(R) == 4 ? 32 : 16; }
 
 __device__ __forceinline__ int xcd_remap(int bid, int total) {
   const int q = total >> 3, r = total & 7;
@@ -93,7 +101,7 @@ __device__ __forceinline__ const char* item_ptr(const Operand& o, const int* ids
 // took more than 256 and ran one wave per SIMD).
 template <typename R, int BM, int BN>
 constexpr int gemm_min_blocks() {
-  const int lds = (int)((160 * 1024) / (2 * 2 * gemm_bk<R>() * ((BM + PAD) + (BN + PAD)) * sizeof(R)));
+  const int lds = (int)((160 * 1024) / (2 * 2 * gemm_bk<R, BM, BN>() * ((BM + PAD) + (BN + PAD)) * sizeof(R)));
   const int regs = sizeof(R) == 8 ? (BM * BN <= 32 * 32 ? 4 : BM * BN <= 64 * 64 ? 3 : 1)
                                    : (BM * BN <= 32 * 32 ? 4 : BM * BN <= 64 * 64 ? 5
                                                             : BM * BN <= 128 * 64 ? 3 : 2);
@@ -101,7 +109,8 @@ constexpr int gemm_min_blocks() {
   return n < 1 ? 1 : n;
 }
 
-template <int TA, int TB, int TC, typename R, int OPA, int OPB, int BM, int BN, int EPI>
+// FAR: operand rows too far apart for a 32-bit window (args.far)
+template <int TA, int TB, int TC, typename R, int OPA, int OPB, int BM, int BN, int EPI, bool FAR>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(gemm_min_blocks<R, BM, BN>(), 8)))
 void gemm_kernel(const GemmArgs args) {
   static_assert(EPI != GEMM_EPI_RIGHT || OPB == OP_N, "the right epilogue maps B's columns");
@@ -109,7 +118,7 @@ void gemm_kernel(const GemmArgs args) {
   using CB = typename Store<TB>::T;
   using CC = typename Store<TC>::T;
   using V = typename Mfma<R>::V;
-  constexpr int BK = gemm_bk<R>();
+  constexpr int BK = gemm_bk<R, BM, BN>();
   constexpr int TPK = NT / BK;       // threads per k row when a row is staged along m / n
   constexpr int EA = BM * BK / NT;   // A elements staged per thread
   constexpr int EB = BN * BK / NT;   // B elements staged per thread
@@ -161,183 +170,68 @@ void gemm_kernel(const GemmArgs args) {
   CC* __restrict__ C = reinterpret_cast<CC*>(const_cast<char*>(item_ptr(G.c, G.ids, item)));
 
   const int tid = threadIdx.x;
-  R ar[EA], ai[EA], br[EB], bi[EB];
-  // complex64 operands whose rows start on 16 bytes are staged two elements
-  // (16 bytes) per load where a thread's run lies inside the matrix
-  constexpr bool PA = sizeof(CA) == 8 && EA % 2 == 0, PB = sizeof(CB) == 8 && EB % 2 == 0;
-  const bool vec_a = PA && lda % 2 == 0 && (reinterpret_cast<unsigned long long>(A) & 15) == 0;
-  const bool vec_b = PB && EPI != GEMM_EPI_RIGHT && ldb % 2 == 0 &&
+  // staging: a thread takes EA (EB) consecutive elements of one line of the
+  // stored operand, lines along m / n (k contiguous) or along k
+  CA ra[EA];
+  CB rb[EB];
+  constexpr bool AK = OPA == OP_N || OPA == OP_J, BKC = OPB == OP_T;   // k contiguous
+  constexpr int TPA = AK ? BK / EA : TPK, TPB = BKC ? BK / EB : TPK;   // threads per line
+  const int la = tid / TPA, qa = (tid % TPA) * EA, lb = tid / TPB, qb = (tid % TPB) * EB;
+  // the right epilogue's tile columns are (t, y), y contiguous in B
+  constexpr bool TY = EPI == GEMM_EPI_RIGHT;
+  static_assert(!TY || (BN / 2) % EB == 0, "a run lies in one t");
+  const int half = N / 2;
+  const int nb = TY ? (qb / (BN / 2)) * half + n0 + qb % (BN / 2) : n0 + qb;   // B's column of element 0
+  const int nleft = TY ? half - (n0 + qb % (BN / 2)) : N - nb;                 // up to the row's end
+  // lines of pairs of complex64 elements (16 bytes)
+  const bool vec_a = sizeof(CA) == 8 && lda % 2 == 0 && (AK ? K : M) % 2 == 0 &&
+                     (reinterpret_cast<unsigned long long>(A) & 15) == 0;
+  const bool vec_b = sizeof(CB) == 8 && ldb % 2 == 0 && (BKC ? K : TY ? half : N) % 2 == 0 &&
                      (reinterpret_cast<unsigned long long>(B) & 15) == 0;
+  const unsigned va = (unsigned)(la * lda + qa) * (unsigned)sizeof(CA);
+  const unsigned vb = (unsigned)(lb * ldb + (BKC ? qb : nb)) * (unsigned)sizeof(CB);
   if constexpr (EPI != GEMM_EPI_NONE) {   // visible after the first barrier
     const CC* __restrict__ W = reinterpret_cast<const CC*>(item_ptr(G.w, nullptr, item));
     const int nw = G.wl * 4 * G.wr;
     for (int i = tid; i < nw; i += NT) sW[i] = W[i];
   }
 
+  // lines of A (B) of the step at k0, and the first one's address: the tile's
+  // rows from column k0 on, or rows k0 .. of the stored K x M (K x N)
   auto load_a = [&](int k0) {
-    if constexpr (OPA == OP_N || OPA == OP_J) {   // stored M x K: EA consecutive k
-      constexpr int TPR = BK / EA;
-      const int row = tid / TPR, kq = (tid % TPR) * EA;
-      const int m = m0 + row;
-      if constexpr (PA) {
-        if (vec_a && m < M && k0 + kq + EA <= K) {
-          const float4* q = reinterpret_cast<const float4*>(A + (long long)m * lda + k0 + kq);
-#pragma unroll
-          for (int u = 0; u < EA / 2; ++u) {
-            const float4 v = q[u];
-            ar[2 * u] = v.x;
-            ai[2 * u] = (OPA == OP_J) ? -v.y : v.y;
-            ar[2 * u + 1] = v.z;
-            ai[2 * u + 1] = (OPA == OP_J) ? -v.w : v.w;
-          }
-          return;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < EA; ++u) {
-        const int k = k0 + kq + u;
-        R re = 0, im = 0;
-        if (m < M && k < K) {
-          const CA v = A[(long long)m * lda + k];
-          re = v.x;
-          im = v.y;
-        }
-        ar[u] = re;
-        ai[u] = (OPA == OP_J) ? -im : im;
-      }
-    } else {  // OP_C: stored K x M, conjugated; EA consecutive m
-      const int kr = tid / TPK, mq = (tid % TPK) * EA;
-      const int k = k0 + kr;
-      if constexpr (PA) {
-        if (vec_a && k < K && m0 + mq + EA <= M) {
-          const float4* q = reinterpret_cast<const float4*>(A + (long long)k * lda + m0 + mq);
-#pragma unroll
-          for (int u = 0; u < EA / 2; ++u) {
-            const float4 v = q[u];
-            ar[2 * u] = v.x;
-            ai[2 * u] = -v.y;
-            ar[2 * u + 1] = v.z;
-            ai[2 * u + 1] = -v.w;
-          }
-          return;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < EA; ++u) {
-        const int m = m0 + mq + u;
-        R re = 0, im = 0;
-        if (m < M && k < K) {
-          const CA v = A[(long long)k * lda + m];
-          re = v.x;
-          im = v.y;
-        }
-        ar[u] = re;
-        ai[u] = -im;
-      }
-    }
-  };
-  auto store_a = [&]() {
-    if constexpr (OPA == OP_N || OPA == OP_J) {
-      constexpr int TPR = BK / EA;
-      const int row = tid / TPR, kq = (tid % TPR) * EA;
-#pragma unroll
-      for (int u = 0; u < EA; ++u) {
-        sA_r[stage][kq + u][row] = ar[u];
-        sA_i[stage][kq + u][row] = ai[u];
-      }
-    } else {
-      const int kr = tid / TPK, mq = (tid % TPK) * EA;
-#pragma unroll
-      for (int u = 0; u < EA; ++u) {
-        sA_r[stage][kr][mq + u] = ar[u];
-        sA_i[stage][kr][mq + u] = ai[u];
-      }
-    }
+    const int lines = AK ? min(BM, M - m0) : min(BK, K - k0);
+    const int left = la < lines ? (AK ? K - k0 : M - m0) - qa : 0;
+    const CA* w = A + (AK ? (long long)m0 * lda + k0 : (long long)k0 * lda + m0);
+    if constexpr (FAR)
+      tl_run_far<CA, EA>(ra, w + (long long)la * lda + qa, left);
+    else
+      tl_run<CA, EA>(ra, tl_rsrc(w, ((long long)(lines - 1) * lda + (AK ? K - k0 : M - m0)) *
+                                        (long long)sizeof(CA)), va, left, vec_a);
   };
   auto load_b = [&](int k0) {
-    if constexpr (OPB == OP_N) {  // stored K x N: EB consecutive n
-      const int kr = tid / TPK, nq = (tid % TPK) * EB;
-      const int k = k0 + kr;
-      if constexpr (PB && EPI != GEMM_EPI_RIGHT) {
-        if (vec_b && k < K && n0 + nq + EB <= N) {
-          const float4* q = reinterpret_cast<const float4*>(B + (long long)k * ldb + n0 + nq);
+    const int lines = BKC ? min(BN, N - n0) : min(BK, K - k0);
+    const int left = lb < lines ? (BKC ? K - k0 - qb : nleft) : 0;
+    const CB* w = B + (BKC ? (long long)n0 * ldb + k0 : (long long)k0 * ldb);
+    if constexpr (FAR)
+      tl_run_far<CB, EB>(rb, w + (long long)lb * ldb + (BKC ? qb : nb), left);
+    else
+      tl_run<CB, EB>(rb, tl_rsrc(w, ((long long)(lines - 1) * ldb + (BKC ? K - k0 : N)) *
+                                        (long long)sizeof(CB)), vb, left, vec_b);
+  };
+  auto store_a = [&]() {
 #pragma unroll
-          for (int u = 0; u < EB / 2; ++u) {
-            const float4 v = q[u];
-            br[2 * u] = v.x;
-            bi[2 * u] = v.y;
-            br[2 * u + 1] = v.z;
-            bi[2 * u + 1] = v.w;
-          }
-          return;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < EB; ++u) {
-        int n = n0 + nq + u;
-        bool inb = n < N;
-        if constexpr (EPI == GEMM_EPI_RIGHT) {   // column (t, y) of the stored (t, y) pairs
-          const int cl = nq + u, half = N / 2, y = n0 + cl % (BN / 2);
-          n = (cl / (BN / 2)) * half + y;
-          inb = y < half;
-        }
-        R re = 0, im = 0;
-        if (inb && k < K) {
-          const CB v = B[(long long)k * ldb + n];
-          re = v.x;
-          im = v.y;
-        }
-        br[u] = re;
-        bi[u] = im;
-      }
-    } else {  // OP_T: stored N x K: EB consecutive k
-      constexpr int TPR = BK / EB;
-      const int nr = tid / TPR, kq = (tid % TPR) * EB;
-      const int n = n0 + nr;
-      if constexpr (PB) {
-        if (vec_b && n < N && k0 + kq + EB <= K) {
-          const float4* q = reinterpret_cast<const float4*>(B + (long long)n * ldb + k0 + kq);
-#pragma unroll
-          for (int u = 0; u < EB / 2; ++u) {
-            const float4 v = q[u];
-            br[2 * u] = v.x;
-            bi[2 * u] = v.y;
-            br[2 * u + 1] = v.z;
-            bi[2 * u + 1] = v.w;
-          }
-          return;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < EB; ++u) {
-        const int k = k0 + kq + u;
-        R re = 0, im = 0;
-        if (n < N && k < K) {
-          const CB v = B[(long long)n * ldb + k];
-          re = v.x;
-          im = v.y;
-        }
-        br[u] = re;
-        bi[u] = im;
-      }
+    for (int u = 0; u < EA; ++u) {
+      const int k = AK ? qa + u : la, m = AK ? la : qa + u;
+      sA_r[stage][k][m] = (R)ra[u].x;
+      sA_i[stage][k][m] = OPA == OP_N ? (R)ra[u].y : -(R)ra[u].y;
     }
   };
   auto store_b = [&]() {
-    if constexpr (OPB == OP_N) {
-      const int kr = tid / TPK, nq = (tid % TPK) * EB;
 #pragma unroll
-      for (int u = 0; u < EB; ++u) {
-        sB_r[stage][kr][nq + u] = br[u];
-        sB_i[stage][kr][nq + u] = bi[u];
-      }
-    } else {
-      constexpr int TPR = BK / EB;
-      const int nr = tid / TPR, kq = (tid % TPR) * EB;
-#pragma unroll
-      for (int u = 0; u < EB; ++u) {
-        sB_r[stage][kq + u][nr] = br[u];
-        sB_i[stage][kq + u][nr] = bi[u];
-      }
+    for (int u = 0; u < EB; ++u) {
+      const int k = BKC ? qb + u : lb, n = BKC ? lb : qb + u;
+      sB_r[stage][k][n] = (R)rb[u].x;
+      sB_i[stage][k][n] = (R)rb[u].y;
     }
   };
 
@@ -576,23 +470,27 @@ void gemm_kernel(const GemmArgs args) {
 template <int TA, int TB, int TC, typename R, int OPA, int OPB, int EPI = GEMM_EPI_NONE>
 hipError_t run(int variant, const GemmArgs& args, hipStream_t s) {
   if (args.total_tiles <= 0) return hipSuccess;
+  if (args.far && variant != GEMM_32x32) return hipErrorInvalidValue;
   const dim3 grid(args.total_tiles), blk(NT);
   switch (variant) {
     case GEMM_64x64:
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 64, EPI>), grid, blk, 0, s, args);
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 64, EPI, false>), grid, blk, 0, s, args);
       break;
     case GEMM_32x32:
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 32, 32, EPI>), grid, blk, 0, s, args);
+      if (args.far)
+        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 32, 32, EPI, true>), grid, blk, 0, s, args);
+      else
+        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 32, 32, EPI, false>), grid, blk, 0, s, args);
       break;
     case GEMM_128x64:
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 64, EPI>), grid, blk, 0, s, args);
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 64, EPI, false>), grid, blk, 0, s, args);
       break;
     case GEMM_64x128:
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 128, EPI>), grid, blk, 0, s, args);
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 128, EPI, false>), grid, blk, 0, s, args);
       break;
     case GEMM_128x128:
       if constexpr (sizeof(R) == 4) {
-        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 128, EPI>), grid, blk, 0, s, args);
+        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 128, EPI, false>), grid, blk, 0, s, args);
         break;
       }
       return hipErrorInvalidValue;

@@ -459,11 +459,13 @@ int run_gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
     int ng = 0;
     long long big = -1;
     TuneKey key{};
+    bool far = false;
     const int epi = jobs[i].epi;   // one epilogue per launch
     for (; j_end < jobs.size() && ng < GEMM_MAX_GROUPS && jobs[j_end].epi == epi; ++j_end) {
       const GemmJob& j = jobs[j_end];
       if (j.batch <= 0 || j.M <= 0 || j.N <= 0) continue;
       ++ng;
+      far = far || j.lda >= GEMM_FAR_LD || j.ldb >= GEMM_FAR_LD;
       const long long w = (long long)j.M * j.N * j.batch;
       if (w > big) {
         big = w;
@@ -476,7 +478,8 @@ int run_gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
       continue;
     }
     bool timed = false;
-    const int variant = tune_choose(ctx, key, &timed);
+    far = far && tacc != ACC_BF16X3;
+    const int variant = far ? GEMM_32x32 : tune_choose(ctx, key, &timed);
     int bm = 64, bn = 64;
     gemm_tile_shape(variant, &bm, &bn);
     GemmArgs args;
@@ -524,6 +527,7 @@ int run_gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
     args.ngroups = ng;
     args.total_tiles = tiles;
     args.epi = epi;
+    args.far = far;
     hipEvent_t ta_ev = nullptr, tb_ev = nullptr;
     if (timed) {
       ta_ev = take_event(ctx);

@@ -174,7 +174,8 @@ int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int
     if ((opa != OP_N && opa != OP_C && opa != OP_J) || (opb != OP_N && opb != OP_T))
       return testing_fail(DCS_EINVAL, "bad op");
     const bool herm = (variant & 16) != 0;
-    variant &= ~16;
+    const bool far = (variant & 32) != 0;
+    variant &= ~48;
     if (variant < 0 || variant >= GEMM_VARIANTS) return testing_fail(DCS_EINVAL, "bad tile shape");
     int bm = 64, bn = 64;
     gemm_tile_shape(variant, &bm, &bn);
@@ -212,6 +213,7 @@ int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int
     g.tile_begin = 0;
     args.ngroups = 1;
     args.total_tiles = g.tiles_per_item * batch;
+    args.far = far;
     hipError_t e = launch_gemm(ta, tb, tc, tacc, opa, opb, variant, args, s);
     if (e == hipErrorInvalidValue) return testing_fail(DCS_EINVAL, "type/op combination not built");
     T_HIP(e);
