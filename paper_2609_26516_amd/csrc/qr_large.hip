@@ -316,36 +316,19 @@ constexpr int QRS_NW = 8, QRS_MAXB = 4;   // 512 threads, rows in 16-row blocks
 constexpr size_t QRS_LDS = (size_t)512 * QB * sizeof(double2) + (size_t)QRS_NW * 256 * sizeof(double2);
 
 // The panel at column p of one matrix, by the whole 512-thread workgroup; P
-// (512 x 16 panel rows) and Wp (8 areas of 256) in LDS.  Uniform early exit
-// when p >= n.
-__device__ __forceinline__ void spread_panel(const QrlItem& it, int p, double2* P, double2* Wp) {
+// (512 x 16 panel rows) and Wp (8 areas of 256) in LDS.  a: the panel's
+// columns, block beta = wave + 8 b of 16 rows in a[b], row 16 beta + 4t + lk,
+// column p + li (zero past row m and column n; blocks above row p not read).
+__device__ __forceinline__ void spread_panel(const QrlItem& it, int p, double2 (&a)[QRS_MAXB][4],
+                                             double2* P, double2* Wp) {
   PanelSmem2<QRS_NW, QB>& psm = *reinterpret_cast<PanelSmem2<QRS_NW, QB>*>(P);
   const int m = it.g->m, n = it.g->n;
-  if (p >= n) return;
-  double2* A = qrl_ws(it);
-  double2* V = A + (long long)m * n;
+  double2* V = qrl_ws(it) + (long long)m * n;
   double2* Tg = V + (long long)m * n;
   const int mp = m - p, nbk = min(QB, n - p), k = p / QB;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lk = lane >> 4;
   const double2 zero = make_double2(0.0, 0.0);
-
-  if (p == 0 && tid == 0) {   // |F|^2 from the chunk partials, in a fixed order
-    const double* part = qrl_partials(A, m, n);
-    double s = 0.0;
-    for (int c = 0; c < QRL_CHUNKS; ++c) s += part[c];
-    *reinterpret_cast<double*>(const_cast<char*>(item_ptr(it.g->nrm2, it.g->ids, it.item))) = s;
-  }
-  double2 a[QRS_MAXB][4];   // rows 16 beta + 4t + lk, column p + li
-#pragma unroll
-  for (int b = 0; b < QRS_MAXB; ++b) {
-    const int beta = wave + QRS_NW * b;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int row = 16 * beta + 4 * t + lk;
-      a[b][t] = (beta >= k && row < m && li < nbk) ? A[(long long)row * n + p + li] : zero;
-    }
-  }
   bool chol = false;
   if (mp > nbk) {
     chol = panel_cholqr<QRS_NW, QRS_MAXB>(a, m, k, mp, nbk, P, Wp);
@@ -380,51 +363,93 @@ __device__ __forceinline__ void spread_panel(const QrlItem& it, int p, double2* 
   if (tid < QB * QB) Tg[(long long)k * QB * QB + tid] = Wp[tid];
 }
 
-__global__ __launch_bounds__(512, 1) void qrs_panel_kernel(const QrArgs args, int p) {
+// The first panel, and |F|^2.
+__global__ __launch_bounds__(512, 1) void qrs_panel_kernel(const QrArgs args) {
   extern __shared__ __attribute__((aligned(16))) double2 qrs_dyn[];
-  spread_panel(qrl_item(args, blockIdx.x), p, qrs_dyn, qrs_dyn + 512 * QB);
+  const QrlItem it = qrl_item(args, blockIdx.x);
+  const int m = it.g->m, n = it.g->n, tid = threadIdx.x;
+  double2* A = qrl_ws(it);
+  if (tid == 0) {   // |F|^2 from the chunk partials, in a fixed order
+    const double* part = qrl_partials(A, m, n);
+    double s = 0.0;
+    for (int c = 0; c < QRL_CHUNKS; ++c) s += part[c];
+    *reinterpret_cast<double*>(const_cast<char*>(item_ptr(it.g->nrm2, it.g->ids, it.item))) = s;
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int li = lane & 15, lk = lane >> 4;
+  double2 a[QRS_MAXB][4];
+#pragma unroll
+  for (int b = 0; b < QRS_MAXB; ++b)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int row = 16 * (wave + QRS_NW * b) + 4 * t + lk;
+      a[b][t] = (row < m && li < n) ? A[(long long)row * n + li] : make_double2(0.0, 0.0);
+    }
+  spread_panel(it, 0, a, qrs_dyn, qrs_dyn + 512 * QB);
 }
 
 // Trailing update of the spread path, one 512-thread workgroup per (16-column
-// strip, matrix): A[p:, c0:c0+16] -= V T^H (V^H A[p:, c0:c0+16]).  Wave w
-// takes panel rows 64w .. 64w + 63 (at most 512 rows); the waves' parts of
-// W = V^H A are summed through LDS in a fixed order.
+// strip, matrix): A[p:, c0:c0+16] -= V T^H (V^H A[p:, c0:c0+16]).  The waves
+// take the 16-row blocks from row p on in turn, in the panel's register
+// layout; their parts of W = V^H A are summed through LDS in a fixed order,
+// and V is kept in LDS for the second product.
 // The workgroup of strip 0, whose columns are the next panel's, then factors
-// that panel (look-ahead): its latency overlaps the other strips' updates,
-// and the next update launch finds V and T in place.
+// that panel from its registers (look-ahead): its latency overlaps the other
+// strips' updates, and the next update launch finds V and T in place.  These
+// workgroups take longest, so the matrices' first strips come first in the
+// grid.  A launch is bounded by this chain: the update's loads and two
+// reductions, then the panel's two one-wave recurrences.  Mean over the
+// launches of a round of 48 states at bonds up to 512: 51.0 us with the next
+// panel read back from memory, V read twice and the matrices' strips in
+// order, 44.7 now.
 __global__ __launch_bounds__(512, 1) void qrs_update_kernel(const QrArgs args, int p) {
   extern __shared__ __attribute__((aligned(16))) double2 qrs_dyn[];
+  double2* sV = qrs_dyn;
   double2 (*sW)[256] = reinterpret_cast<double2 (*)[256]>(qrs_dyn + 512 * QB);
-  const QrlItem it = qrl_item(args, blockIdx.y);
+  const QrlItem it = qrl_item(args, blockIdx.x);
+  const int strip = blockIdx.y;
   const int m = it.g->m, n = it.g->n;
-  const int c0 = p + QB + 16 * blockIdx.x;
+  const int c0 = p + QB + 16 * strip;
   if (p >= n || c0 >= n) return;   // uniform over the workgroup
   double2* A = qrl_ws(it);
   const double2* V = A + (long long)m * n;
-  const double2* T = V + (long long)m * n + (long long)(p / QB) * QB * QB;
-  const int mp = m - p, nbk = min(QB, n - p);
+  const int k0 = p / QB;
+  const double2* T = V + (long long)m * n + (long long)k0 * QB * QB;
+  const int nbk = min(QB, n - p);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lk = lane >> 4;
   const int col = c0 + li;
   const bool col_ok = col < n;
-  const int r0 = 64 * wave, r1 = min(mp, r0 + 64);
   const double2 zero = make_double2(0.0, 0.0);
-  // this wave's rows of the strip (row r0 + 16h + 4t + lk) and its part of W
-  double2 av[4][4];
+  // this wave's rows of the strip (block beta = wave + 8 h, row 16 beta + 4t +
+  // lk) and its part of W.  V's block beta goes to place beta - k0 - 1 (mod
+  // 32) of the LDS rows: the next panel puts the same wave's rows there.
+  double2 av[QRS_MAXB][4], tt[4];
   CAcc3 w;
   w.zero();
 #pragma unroll
-  for (int h = 0; h < 4; ++h) {
+  for (int h = 0; h < QRS_MAXB; ++h) {
+    const int beta = wave + QRS_NW * h;
+    const bool on = beta >= k0 && 16 * beta < m;   // uniform over the wave
     double2 vw[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int i = r0 + 16 * h + 4 * t + lk;
-      av[h][t] = (i < r1 && col_ok) ? A[(long long)(p + i) * n + col] : zero;
-      vw[t] = (i < r1 && li < nbk) ? V[(long long)(p + i) * n + p + li] : zero;
+      const int row = 16 * beta + 4 * t + lk;
+      av[h][t] = (on && row < m && col_ok) ? A[(long long)row * n + col] : zero;
+      vw[t] = (on && row < m && li < nbk) ? V[(long long)row * n + p + li] : zero;
     }
+    if (on) {
+      const int b0 = 16 * ((beta - k0 - 1) & 31);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) w.add(vw[t].x, -vw[t].y, av[h][t].x, av[h][t].y);
+      for (int t = 0; t < 4; ++t) {
+        sV[pidx(b0 + 4 * t + lk, li)] = vw[t];
+        w.add(vw[t].x, -vw[t].y, av[h][t].x, av[h][t].y);
+      }
+    }
   }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    tt[t] = (li < nbk && 4 * t + lk < nbk) ? T[(4 * t + lk) * QB + li] : zero;
 #pragma unroll
   for (int r = 0; r < 4; ++r) sW[wave][(lk + 4 * r) * 16 + li] = make_double2(w.re(r), w.im(r));
   __syncthreads();
@@ -438,25 +463,13 @@ __global__ __launch_bounds__(512, 1) void qrs_update_kernel(const QrArgs args, i
     sW[0][tid] = sum;
   }
   __syncthreads();
-  v4d_t wr, wi;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const double2 x = sW[0][(lk + 4 * t) * 16 + li];
-    wr[t] = x.x;
-    wi[t] = x.y;
-  }
   // W2 = T^H W (item t = row lk + 4t = the B operand of k-step t)
   CAcc3 x2;
   x2.zero();
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int sr = 4 * t + lk;
-    double2 x = zero;
-    if (li < nbk && sr < nbk) {
-      const double2 tt = T[sr * QB + li];
-      x = make_double2(tt.x, -tt.y);
-    }
-    x2.add(x.x, x.y, wr[t], wi[t]);
+    const double2 x = sW[0][(lk + 4 * t) * 16 + li];
+    x2.add(tt[t].x, -tt[t].y, x.x, x.y);
   }
   double x2r[4], x2i[4];
 #pragma unroll
@@ -466,30 +479,29 @@ __global__ __launch_bounds__(512, 1) void qrs_update_kernel(const QrArgs args, i
   }
   // A -= V W2, block by block
 #pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int rb = r0 + 16 * h;
-    if (rb >= r1) break;   // uniform over the wave
-    CAcc3 e;
-    e.zero();
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int i = rb + li, sr = 4 * t + lk;
-      const double2 v = (i < r1 && sr < nbk) ? V[(long long)(p + i) * n + p + sr] : zero;
-      e.add(v.x, v.y, x2r[t], x2i[t]);
-    }
-    if (col_ok) {
+  for (int h = 0; h < QRS_MAXB; ++h) {
+    const int beta = wave + QRS_NW * h;
+    if (beta >= k0 && 16 * beta < m) {
+      const int b0 = 16 * ((beta - k0 - 1) & 31);
+      CAcc3 e;
+      e.zero();
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const int i = rb + lk + 4 * t;
-        if (i < r1)
-          A[(long long)(p + i) * n + col] = make_double2(av[h][t].x - e.re(t), av[h][t].y - e.im(t));
+        const double2 v = sV[pidx(b0 + li, 4 * t + lk)];
+        e.add(v.x, v.y, x2r[t], x2i[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        av[h][t] = make_double2(av[h][t].x - e.re(t), av[h][t].y - e.im(t));
+        const int row = 16 * beta + 4 * t + lk;
+        if (strip > 0 && col_ok && row < m) A[(long long)row * n + col] = av[h][t];
       }
     }
   }
-  if (blockIdx.x == 0) {   // the next panel (columns c0 .. c0 + 15, just updated)
-    __threadfence_block();
-    __syncthreads();
-    spread_panel(it, c0, qrs_dyn, qrs_dyn + 512 * QB);
+  // the next panel: its columns stay in registers (nothing else reads them)
+  if (strip == 0) {
+    __syncthreads();   // W is read everywhere before its place is reused
+    spread_panel(it, c0, av, qrs_dyn, qrs_dyn + 512 * QB);
   }
 }
 
@@ -786,9 +798,9 @@ hipError_t run_spread(QrArgs args, int items, int m_max, int n_max, hipStream_t 
   if (attr2 != hipSuccess) return attr2;
   const dim3 chunks(QRL_CHUNKS, items);
   hipLaunchKernelGGL((qrl_load_kernel<CTI>), chunks, dim3(256), 0, s, args);
-  hipLaunchKernelGGL(qrs_panel_kernel, dim3(items), dim3(512), QRS_LDS, s, args, 0);
+  hipLaunchKernelGGL(qrs_panel_kernel, dim3(items), dim3(512), QRS_LDS, s, args);
   for (int p = 0; p + QB < n_max; p += QB)   // update by panel p, factor panel p + 16
-    hipLaunchKernelGGL(qrs_update_kernel, dim3((n_max - p - QB + 15) / 16, items), dim3(512), QRS_LDS,
+    hipLaunchKernelGGL(qrs_update_kernel, dim3(items, (n_max - p - QB + 15) / 16), dim3(512), QRS_LDS,
                        s, args, p);
   return hipGetLastError();
 }
