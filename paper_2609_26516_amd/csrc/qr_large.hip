@@ -15,15 +15,20 @@
 //              256-row chunk (m > 512) or per matrix (m <= 512); writes the
 //              explicit V (unit diagonal) and T
 //   qrl_wpart  W = V^H A[p:, c:] in parts over (16-column strip, 256-row
-//   qrl_update chunk) tiles on FP64 MFMA, then A[p:, c:] -= V X W with
-//              X = T^H, every chunk summing its strip's parts in one order
-// After the last panel A is reset to [I; 0] and the panels are applied in
-// reverse order with X = T, which leaves the thin Q = H_0 ... H_{n-1} [I; 0]
-// in A; qrl_store writes Q (mode 0) or Q^H (mode 1) in the output precision.
+//   qrl_update chunk) tiles on FP64 MFMA, then A[p:, c:] -= V T^H W, every
+//              chunk summing its strip's parts in one order
+// After the last panel A is reset to [I; 0] and the reflectors are applied in
+// reverse order, four panels at a time, which leaves the thin Q = H_0 ...
+// H_{n-1} [I; 0] in A:
+//   qrq_merge  the T factors of each four panels joined to one of 64 x 64
+//   qrq_wpart  W = V^H A[p:, p:] for the four panels' 64 columns of V, and
+//   qrq_update A[p:, p:] -= V T W
+// qrl_store writes Q (mode 0) or Q^H (mode 1) in the output precision.
 #include "dcs_internal.h"
 #include "kernel_util.h"
 #include "qr_panel.h"
 #include "qr_cholpanel.h"
+#include "tile_load.h"
 
 namespace dcs {
 namespace {
@@ -78,11 +83,10 @@ __global__ __launch_bounds__(256) void qrl_load_kernel(const QrArgs args) {
   if (threadIdx.x == 0) qrl_partials(A, m, n)[blockIdx.x] = part;
 }
 
-// A[p:, c0:c0+16] -= V X (V^H A[p:, c0:c0+16]) with X = T^H (conj_t) or T,
-// in two launches over (16-column strip, QRL_CH-row chunk) tiles so the chip
+// A[p:, c0:c0+16] -= V T^H (V^H A[p:, c0:c0+16]), in two launches over (16-column strip, QRL_CH-row chunk) tiles so the chip
 // has many waves in flight: qrl_wpart writes each chunk's W = V^H A part,
 // qrl_update sums the parts of its strip in chunk order (the same sum in
-// every chunk of the strip), forms X W and updates its rows.
+// every chunk of the strip), forms T^H W and updates its rows.
 constexpr int QRL_CH = 256;   // rows per chunk (four waves of 64)
 
 __device__ __forceinline__ double2* qrl_wparts(double2* ws, int m, int n) {
@@ -101,11 +105,11 @@ __device__ __forceinline__ double2* qrt_scratch(double2* ws, int m, int n) {
 }
 
 template <int NB>
-__global__ __launch_bounds__(256) void qrl_wpart_kernel(const QrArgs args, int p, int c_off) {
+__global__ __launch_bounds__(256) void qrl_wpart_kernel(const QrArgs args, int p) {
   __shared__ double2 sW[4][256];
   const QrlItem it = qrl_item(args, blockIdx.z);
   const int m = it.g->m, n = it.g->n;
-  const int c0 = p + c_off + 16 * blockIdx.x;
+  const int c0 = p + NB + 16 * blockIdx.x;
   const int mp = m - p;
   if (p >= n || c0 >= n || (int)blockIdx.y * QRL_CH >= mp) return;
   double2* A = qrl_ws(it);
@@ -143,17 +147,15 @@ __global__ __launch_bounds__(256) void qrl_wpart_kernel(const QrArgs args, int p
   qrl_wparts(A, m, n)[((long long)blockIdx.x * nchunk + blockIdx.y) * 256 + e] = sum;
 }
 
-// In the forward pass (c_off = NB) the strip-0 workgroups, which update the
-// next panel's columns, also leave that panel's G1 part of their rows (those
+// The strip-0 workgroups, which update the next panel's columns, also leave that panel's G1 part of their rows (those
 // below the next panel's first row) in the split panel's scratch.
 template <int NB>
-__global__ __launch_bounds__(256) void qrl_update_kernel(const QrArgs args, int p, int c_off,
-                                                         int conj_t) {
+__global__ __launch_bounds__(256) void qrl_update_kernel(const QrArgs args, int p) {
   __shared__ double2 sW[256];
   __shared__ double2 sG[4 * 256];
   const QrlItem it = qrl_item(args, blockIdx.z);
   const int m = it.g->m, n = it.g->n;
-  const int c0 = p + c_off + 16 * blockIdx.x;
+  const int c0 = p + NB + 16 * blockIdx.x;
   const int mp = m - p;
   if (p >= n || c0 >= n || (int)blockIdx.y * QRL_CH >= mp) return;
   double2* A = qrl_ws(it);
@@ -184,21 +186,14 @@ __global__ __launch_bounds__(256) void qrl_update_kernel(const QrArgs args, int 
     wr[t] = w.x;
     wi[t] = w.y;
   }
-  // W2 = X W (result item t = row lk + 4t = the B operand of k-step t)
+  // W2 = T^H W (result item t = row lk + 4t = the B operand of k-step t)
   CAcc3 x2;
   x2.zero();
 #pragma unroll
   for (int t = 0; t < NB / 4; ++t) {
     const int s = 4 * t + lk;
     double2 x = zero;
-    if (li < nbk && s < nbk) {
-      if (conj_t) {
-        const double2 tt = T[s * NB + li];
-        x = make_double2(tt.x, -tt.y);
-      } else {
-        x = T[li * NB + s];
-      }
-    }
+    if (li < nbk && s < nbk) x = cconj(T[s * NB + li]);
     x2.add(x.x, x.y, wr[t], wi[t]);
   }
   double xr[4], xi[4];
@@ -225,7 +220,7 @@ __global__ __launch_bounds__(256) void qrl_update_kernel(const QrArgs args, int 
       vv[h][t] = (i < r1 && sref < nbk) ? V[(long long)(p + i) * n + p + sref] : zero;
     }
   }
-  const bool gram = c_off == NB && blockIdx.x == 0;   // uniform
+  const bool gram = blockIdx.x == 0;   // uniform
   CAcc3 g;
   g.zero();
   bool z = false;
@@ -265,6 +260,275 @@ __global__ __launch_bounds__(256) void qrl_update_kernel(const QrArgs args, int 
 #pragma unroll
     for (int w = 1; w < 4; ++w) sum = make_double2(sum.x + sG[w * 256 + e].x, sum.y + sG[w * 256 + e].y);
     qrt_scratch(A, m, n)[blockIdx.y * 256 + e] = sum;
+  }
+}
+
+// Q formation, four panels (64 columns of V) at a time: the working matrix is
+// read and written once per four panels instead of once per panel, which is
+// what bounds it (2048 x 1024, the last step's 33 MB each way: 124 us for four
+// panels one by one, 49 now; a round at bond 1024: 11 ms of these kernels
+// before, 5.1 now with qrq_merge).  A superpanel is as many panels as the W
+// parts of one row chunk fit into the workspace of the single panels' parts:
+// three for matrices of at most 768 rows.  Matrices of at most 64 columns are
+// taken panel by panel: with one superpanel little is saved on the working
+// matrix, and its T is not worth joining (64 matrices of up to 2048 x 32, a
+// tree network's pass: 4.8 ms joined, 2.3 panel by panel).
+struct QrqShape {
+  int np, nch;   // panels of a superpanel, row chunks of its W (np nch <= 256-row chunks)
+};
+__host__ __device__ __forceinline__ QrqShape qrq_shape(int m, int n) {
+  const int c = (m + QRL_CH - 1) / QRL_CH;
+  QrqShape q;
+  q.np = n <= 4 * QB ? 1 : c < 4 ? c : 4;
+  q.nch = c / (q.np == 1 ? 2 : 4);
+  if (q.nch < 1) q.nch = 1;
+  return q;
+}
+
+// V[row][col] of the m x n area behind w, zero where not ok
+__device__ __forceinline__ double2 qrq_v(__amdgpu_buffer_rsrc_t w, int n, int row, int col, bool ok) {
+  double2 v[1];
+  tl_run<double2, 1>(v, w, (unsigned)(row * n + col) * 16u, ok ? 1 : 0, false);
+  return v[0];
+}
+
+// Block (i, j), i <= j, of the superpanel's T, element (r, c): the diagonal
+// blocks are the panels' own, the others lie in V above their panel's top,
+// which holds no part of V (readers of V take it as zero).
+__device__ __forceinline__ double2 qrq_t(const double2* V, const double2* Tg, int n, int P, int i,
+                                         int j, int r, int c) {
+  if (P + 16 * i + r >= n || P + 16 * j + c >= n) return make_double2(0.0, 0.0);
+  return i == j ? Tg[(long long)(P / QB + i) * QB * QB + r * QB + c]
+                : V[(long long)(P + 16 * i + r) * n + P + 16 * j + c];
+}
+
+// One 512-thread workgroup per superpanel: G_ij = V_i^H V_j over the rows
+// below, then column block by column block T_ij = -sum_l T_il G_lj T_jj.
+__global__ __launch_bounds__(512, 1) void qrq_merge_kernel(const QrArgs args) {
+  __shared__ __attribute__((aligned(16))) double2 sP[8 * 256];   // the waves' parts, then G_lj T_jj
+  __shared__ __attribute__((aligned(16))) double2 sG[6 * 256];   // G_ij, then T_ij, at j (j - 1) / 2 + i
+  const QrlItem it = qrl_item(args, blockIdx.y);
+  const int m = it.g->m, n = it.g->n;
+  const QrqShape q = qrq_shape(m, n);
+  const int P = 16 * q.np * blockIdx.x;
+  const int nb = min(q.np, (n - P + 15) / 16);
+  if (nb < 2) return;   // uniform over the workgroup
+  double2* A = qrl_ws(it);
+  double2* V = A + (long long)m * n;
+  const double2* Tg = V + (long long)m * n;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lk = lane >> 4;
+  const __amdgpu_buffer_rsrc_t rV = tl_rsrc(V, (long long)m * n * 16);
+  CAcc3 g[6];
+#pragma unroll
+  for (int e = 0; e < 6; ++e) g[e].zero();
+  for (int rb = P + 16 + 16 * wave; rb < m; rb += 128) {
+    double2 v[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int row = rb + 4 * t + lk, col = P + 16 * i + li;
+        v[i][t] = qrq_v(rV, n, row, col, i < nb && rb >= P + 16 * i && row < m && col < n);
+      }
+    static_for<4>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      static_for<j>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          g[j * (j - 1) / 2 + i].add(v[i][t].x, -v[i][t].y, v[j][t].x, v[j][t].y);
+      });
+    });
+  }
+#pragma unroll
+  for (int e = 0; e < 6; ++e) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      sP[wave * 256 + (lk + 4 * r) * 16 + li] = make_double2(g[e].re(r), g[e].im(r));
+    __syncthreads();
+    if (tid < 256) {
+      double2 s = sP[tid];
+#pragma unroll
+      for (int w = 1; w < 8; ++w) s = make_double2(s.x + sP[w * 256 + tid].x, s.y + sP[w * 256 + tid].y);
+      sG[e * 256 + tid] = s;
+    }
+    __syncthreads();
+  }
+  for (int j = 1; j < nb; ++j) {
+    if (wave < j) {   // X_l = G_lj T_jj, l = wave
+      CAcc3 x;
+      x.zero();
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const double2 a = sG[(j * (j - 1) / 2 + wave) * 256 + li * 16 + 4 * s + lk];
+        const double2 b = qrq_t(V, Tg, n, P, j, j, 4 * s + lk, li);
+        x.add(a.x, a.y, b.x, b.y);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sP[wave * 256 + (lk + 4 * r) * 16 + li] = make_double2(x.re(r), x.im(r));
+    }
+    __syncthreads();
+    if (wave < j) {   // T_ij, i = wave
+      CAcc3 x;
+      x.zero();
+      for (int l = wave; l < j; ++l) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const double2 a = l == wave ? qrq_t(V, Tg, n, P, l, l, li, 4 * s + lk)
+                                      : sG[(l * (l - 1) / 2 + wave) * 256 + li * 16 + 4 * s + lk];
+          const double2 b = sP[l * 256 + (4 * s + lk) * 16 + li];
+          x.add(a.x, a.y, b.x, b.y);
+        }
+      }
+      const int col = P + 16 * j + li;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 t = make_double2(-x.re(r), -x.im(r));
+        sG[(j * (j - 1) / 2 + wave) * 256 + (lk + 4 * r) * 16 + li] = t;
+        if (col < n) V[(long long)(P + 16 * wave + lk + 4 * r) * n + col] = t;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// W = V_b^H A[P:, c0:c0+16] for panel b of the superpanel over one row chunk,
+// one 512-thread workgroup per (strip, chunk and panel).
+__global__ __launch_bounds__(512, 1) void qrq_wpart_kernel(const QrArgs args, int step) {
+  __shared__ __attribute__((aligned(16))) double2 sW[8 * 256];
+  const QrlItem it = qrl_item(args, blockIdx.z);
+  const int m = it.g->m, n = it.g->n;
+  const QrqShape q = qrq_shape(m, n);
+  const int P = 16 * q.np * step, mp = m - P;
+  const int c0 = P + 16 * blockIdx.x, b = blockIdx.y % q.np, chunk = blockIdx.y / q.np;
+  if (c0 >= n || P + 16 * b >= n || chunk >= q.nch) return;   // uniform
+  double2* A = qrl_ws(it);
+  const double2* V = A + (long long)m * n;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lk = lane >> 4;
+  const int col = c0 + li, vcol = P + 16 * b + li;
+  const int rows = ((mp + q.nch - 1) / q.nch + 63) / 64 * 64;   // of a chunk
+  const int end = min(mp, (chunk + 1) * rows);
+  const double2 zero = make_double2(0.0, 0.0);
+  CAcc3 w;
+  w.zero();
+  for (int r0 = chunk * rows + 64 * wave; r0 < end; r0 += 512) {
+    double2 vv[16], bb[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int i = r0 + 4 * u + lk;
+      vv[u] = (i < end && r0 + 4 * u >= 16 * b && vcol < n) ? V[(long long)(P + i) * n + vcol] : zero;
+      bb[u] = (i < end && col < n) ? A[(long long)(P + i) * n + col] : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) w.add(vv[u].x, -vv[u].y, bb[u].x, bb[u].y);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) sW[wave * 256 + (lk + 4 * t) * 16 + li] = make_double2(w.re(t), w.im(t));
+  __syncthreads();
+  if (tid < 256) {
+    double2 sum = sW[tid];
+#pragma unroll
+    for (int u = 1; u < 8; ++u) sum = make_double2(sum.x + sW[u * 256 + tid].x, sum.y + sW[u * 256 + tid].y);
+    qrl_wparts(A, m, n)[((long long)(blockIdx.x * q.nch + chunk) * q.np + b) * 256 + tid] = sum;
+  }
+}
+
+// A[P:, c0:c0+16] -= V T W, one 256-thread workgroup per (strip, 256 rows):
+// the parts of W summed in chunk order, wave i forms rows 16 i .. of T W, and
+// every wave updates 64 rows.  NP: panels of the launch's superpanels, at most.
+template <int NP>
+__global__ __launch_bounds__(256) void qrq_update_kernel(const QrArgs args, int step) {
+  __shared__ __attribute__((aligned(16))) double2 sW[NP * 256];
+  __shared__ __attribute__((aligned(16))) double2 sX[NP * 256];
+  const QrlItem it = qrl_item(args, blockIdx.z);
+  const int m = it.g->m, n = it.g->n;
+  const QrqShape q = qrq_shape(m, n);
+  const int P = 16 * q.np * step, mp = m - P;
+  const int c0 = P + 16 * blockIdx.x;
+  if (c0 >= n || (int)blockIdx.y * QRL_CH >= mp) return;   // uniform
+  double2* A = qrl_ws(it);
+  const double2* V = A + (long long)m * n;
+  const double2* Tg = V + (long long)m * n;
+  const int nb = min(q.np, (n - P + 15) / 16);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lk = lane >> 4;
+  const int col = c0 + li;
+  const bool col_ok = col < n;
+  const double2 zero = make_double2(0.0, 0.0);
+  const int r0 = blockIdx.y * QRL_CH + wave * 64, r1 = min(mp, r0 + 64);
+  const __amdgpu_buffer_rsrc_t rV = tl_rsrc(V, (long long)m * n * 16);
+  const __amdgpu_buffer_rsrc_t rA = tl_rsrc(A, (long long)m * n * 16);
+  double2 av[4][4], vv[4 * NP];
+#pragma unroll
+  for (int h = 0; h < 4; ++h)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int i = r0 + 16 * h + lk + 4 * t;
+      av[h][t] = qrq_v(rA, n, P + i, col, i < r1 && col_ok);
+    }
+  auto load_v = [&](int rb) {   // V's rows rb .. rb + 15, panel b in vv[4b ..]
+#pragma unroll
+    for (int u = 0; u < 4 * NP; ++u) {
+      const int vcol = P + 4 * u + lk;
+      vv[u] = qrq_v(rV, n, P + rb + li, vcol,
+                    (u >> 2) < nb && rb >= 16 * (u >> 2) && rb + li < r1 && vcol < n);
+    }
+  };
+  load_v(r0);
+  {
+    const double2* parts = qrl_wparts(A, m, n) + (long long)blockIdx.x * q.nch * q.np * 256;
+#pragma unroll
+    for (int b = 0; b < NP; ++b) {
+      double2 sum = zero;
+      if (b < nb) {
+        sum = parts[b * 256 + tid];
+        for (int c = 1; c < q.nch; ++c) {
+          const double2 x = parts[(c * q.np + b) * 256 + tid];
+          sum = make_double2(sum.x + x.x, sum.y + x.y);
+        }
+      }
+      sW[b * 256 + tid] = sum;
+    }
+  }
+  __syncthreads();
+  if (wave < NP) {
+    CAcc3 x;
+    x.zero();
+    for (int j = wave; j < nb; ++j) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const double2 a = qrq_t(V, Tg, n, P, wave, j, li, 4 * s + lk);
+        const double2 b = sW[j * 256 + (4 * s + lk) * 16 + li];
+        x.add(a.x, a.y, b.x, b.y);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sX[wave * 256 + (lk + 4 * r) * 16 + li] = make_double2(x.re(r), x.im(r));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    const int rb = r0 + 16 * h;
+    if (rb >= r1) break;   // uniform over the wave
+    CAcc3 e;
+    e.zero();
+#pragma unroll
+    for (int u = 0; u < 4 * NP; ++u) {
+      const double2 x = sX[(u >> 2) * 256 + (lk + 4 * (u & 3)) * 16 + li];   // (zero past the last panel)
+      e.add(vv[u].x, vv[u].y, x.x, x.y);
+    }
+    if (h < 3) load_v(rb + 16);
+    if (col_ok) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int i = rb + lk + 4 * t;
+        if (i < r1)
+          A[(long long)(P + i) * n + col] = make_double2(av[h][t].x - e.re(t), av[h][t].y - e.im(t));
+      }
+    }
   }
 }
 
@@ -778,15 +1042,33 @@ hipError_t run_tall(QrArgs args, int items, int m_max, int n_max, hipStream_t s)
     const int strips = (n_max - p - QB + 15) / 16;
     if (strips > 0) {
       const dim3 grid(strips, (m_max - p + QRL_CH - 1) / QRL_CH, items);
-      hipLaunchKernelGGL((qrl_wpart_kernel<QB>), grid, dim3(256), 0, s, args, p, QB);
-      hipLaunchKernelGGL((qrl_update_kernel<QB>), grid, dim3(256), 0, s, args, p, QB, 1);
+      hipLaunchKernelGGL((qrl_wpart_kernel<QB>), grid, dim3(256), 0, s, args, p);
+      hipLaunchKernelGGL((qrl_update_kernel<QB>), grid, dim3(256), 0, s, args, p);
     }
   }
   hipLaunchKernelGGL(qrl_fill_kernel, chunks, dim3(256), 0, s, args);
-  for (int p = ((n_max - 1) / QB) * QB; p >= 0; p -= QB) {
-    const dim3 grid((n_max - p + 15) / 16, (m_max - p + QRL_CH - 1) / QRL_CH, items);
-    hipLaunchKernelGGL((qrl_wpart_kernel<QB>), grid, dim3(256), 0, s, args, p, 0);
-    hipLaunchKernelGGL((qrl_update_kernel<QB>), grid, dim3(256), 0, s, args, p, 0, 0);
+  // Q: superpanels in reverse, at most `steps` of `width` columns or more each
+  int width = 4 * QB, steps = 0;
+  int chunks_w = 1;
+  bool joined = false;
+  for (int g = 0; g < args.ngroups; ++g) {
+    const QrqShape q = qrq_shape(args.g[g].m, args.g[g].n);
+    width = min(width, q.np * QB);
+    steps = max(steps, (args.g[g].n + q.np * QB - 1) / (q.np * QB));
+    chunks_w = max(chunks_w, q.nch);
+    joined = joined || q.np > 1;
+  }
+  if (joined) hipLaunchKernelGGL(qrq_merge_kernel, dim3(steps, items), dim3(512), 0, s, args);
+  for (int step = steps - 1; step >= 0; --step) {
+    const int p = step * width;   // no superpanel of this step starts above
+    const int strips = (n_max - p + 15) / 16;
+    hipLaunchKernelGGL(qrq_wpart_kernel, dim3(strips, (joined ? 4 : 1) * chunks_w, items), dim3(512), 0,
+                       s, args, step);
+    const dim3 grid(strips, (m_max - p + QRL_CH - 1) / QRL_CH, items);
+    if (joined)
+      hipLaunchKernelGGL(qrq_update_kernel<4>, grid, dim3(256), 0, s, args, step);
+    else
+      hipLaunchKernelGGL(qrq_update_kernel<1>, grid, dim3(256), 0, s, args, step);
   }
   hipLaunchKernelGGL((qrl_store_kernel<CTO>), chunks, dim3(256), 0, s, args);
   return hipGetLastError();
