@@ -769,33 +769,34 @@ __global__ __launch_bounds__(512, 1) void qrs_update_kernel(const QrArgs args, i
   }
 }
 
-// Column-by-column factorisation of the panel rows of A (512 < m <= 2048
-// rows, four rows per thread of a 512-thread workgroup), for panels the
-// Cholesky QR does not take: writes V (unit diagonal) and T.  sP (16 QB
-// values) and sWp (8 x 256) are its LDS scratch.
-constexpr int QRT_RP = 4;   // rows per thread (2048 rows)
-
-__device__ __noinline__ void tall_fallback(const double2* A, double2* V, double2* Tg, int p, int n,
-                                           int mp, int nbk, int k, double2* sP, double2* sWp) {
-  static_assert(sizeof(PanelSmem2<QRS_NW, QB>) <= 16 * QB * sizeof(double2), "fallback scratch fits");
-  PanelSmem2<QRS_NW, QB>& psm = *reinterpret_cast<PanelSmem2<QRS_NW, QB>*>(sP);
+// Column-by-column factorisation of the panel rows of A (m <= 2048 rows, RP
+// rows per thread of a 512-thread workgroup), for panels the Cholesky QR does
+// not take: writes V (unit diagonal) and T.  sP (16 QB values) and sWp
+// (8 x 256) are its LDS scratch.  The panel is held in registers, 4 RP NB of a
+// thread's 256, so the sizes at hand choose RP and NB: 2048 x 16 spills, and
+// with every panel in that form 64 matrices of 2048 x 8 took 380 us, 150 now.
+template <int RP, int NB>
+__device__ __noinline__ void tall_columns(const double2* A, double2* V, double2* Tg, int p, int n,
+                                          int mp, int nbk, int k, double2* sP, double2* sWp) {
+  static_assert(sizeof(PanelSmem2<QRS_NW, NB>) <= 16 * QB * sizeof(double2), "fallback scratch fits");
+  PanelSmem2<QRS_NW, NB>& psm = *reinterpret_cast<PanelSmem2<QRS_NW, NB>*>(sP);
   const int tid = threadIdx.x;
   const double2 zero = make_double2(0.0, 0.0);
-  double2 a[QRT_RP][QB];
+  double2 a[RP][NB];
 #pragma unroll
-  for (int r = 0; r < QRT_RP; ++r) {
+  for (int r = 0; r < RP; ++r) {
     const int i = tid + r * 512;
 #pragma unroll
-    for (int c = 0; c < QB; ++c)
+    for (int c = 0; c < NB; ++c)
       a[r][c] = (i < mp && c < nbk) ? A[(long long)(p + i) * n + p + c] : zero;
   }
-  factor_panel2<QRT_RP, QB, 512>(a, mp, nbk, psm, sWp);
+  factor_panel2<RP, NB, 512>(a, mp, nbk, psm, sWp);
 #pragma unroll
-  for (int r = 0; r < QRT_RP; ++r) {
+  for (int r = 0; r < RP; ++r) {
     const int i = tid + r * 512;
     if (i < mp) {
 #pragma unroll
-      for (int c = 0; c < QB; ++c) {
+      for (int c = 0; c < NB; ++c) {
         if (c < nbk) {
           const double2 v = (i < c) ? zero : (i == c ? make_double2(1.0, 0.0) : a[r][c]);
           V[(long long)(p + i) * n + p + c] = v;
@@ -803,7 +804,20 @@ __device__ __noinline__ void tall_fallback(const double2* A, double2* V, double2
       }
     }
   }
-  if (tid < QB * QB) Tg[(long long)k * QB * QB + tid] = sWp[tid];
+  if (tid < QB * QB) {
+    const int r = tid / QB, c = tid % QB;
+    Tg[(long long)k * QB * QB + tid] = r < NB && c < NB ? sWp[r * NB + c] : zero;
+  }
+}
+
+__device__ __forceinline__ void tall_fallback(const double2* A, double2* V, double2* Tg, int p, int n,
+                                              int mp, int nbk, int k, double2* sP, double2* sWp) {
+  if (nbk <= 8)
+    tall_columns<4, 8>(A, V, Tg, p, n, mp, nbk, k, sP, sWp);
+  else if (mp <= 1024)
+    tall_columns<2, QB>(A, V, Tg, p, n, mp, nbk, k, sP, sWp);
+  else
+    tall_columns<4, QB>(A, V, Tg, p, n, mp, nbk, k, sP, sWp);
 }
 
 // Panel factorisation for 512 < m <= 2048 rows: Cholesky QR twice and
