@@ -30,7 +30,8 @@ extern "C" {
  * those below it also write their conjugate transpose above it, so C is
  * exactly Hermitian when the product is Hermitian; plus 32 (32x32 tiles only)
  * for the form with 64-bit addresses, taken for operands whose rows are 2^21
- * elements apart or more. */
+ * elements apart or more; plus 64 (128) to conjugate A (B) on top of its op,
+ * not in the split-BF16 form. */
 int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int N, int K,
                   int batch, int variant, const double *A, const double *B, double *C,
                   void *stream);

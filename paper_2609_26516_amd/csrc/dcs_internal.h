@@ -41,8 +41,12 @@ struct GemmGroup {
   // and below the diagonal are computed, tiles_per_item = T (T + 1) / 2 for
   // T tile rows; each tile below the diagonal also writes its conjugate
   // transpose above it
-  int herm, pad_;
+  int herm;
+  // GEMM_FLIP_*: that operand is conjugated on top of its op (not in the
+  // split-BF16 form)
+  int flip;
 };
+enum { GEMM_FLIP_A = 1, GEMM_FLIP_B = 2 };
 
 constexpr int GEMM_MAX_GROUPS = 16;
 // Epilogues: none (C = op(A) op(B)), or the gate operator of a site applied

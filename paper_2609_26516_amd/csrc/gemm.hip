@@ -27,7 +27,9 @@
 //
 // Every group of a launch is a batch of equal-shape problems; item b of a
 // group addresses its operands through the slot-id table or its call-local
-// index, with stride 0 for an operand shared by all items.
+// index, with stride 0 for an operand shared by all items.  A group may flip
+// the conjugation of its operands, so that every layout of A and B exists
+// with and without it.
 #include "dcs_internal.h"
 #include "tile_load.h"
 
@@ -218,12 +220,15 @@ void gemm_kernel(const GemmArgs args) {
       tl_run<CB, EB>(rb, tl_rsrc(w, ((long long)(lines - 1) * ldb + (BKC ? K - k0 : N)) *
                                         (long long)sizeof(CB)), vb, left, vec_b);
   };
+  // signs of the imaginary parts: the op's conjugation and the group's flips
+  const R fa = (OPA == OP_N) == ((G.flip & GEMM_FLIP_A) == 0) ? R(1) : R(-1);
+  const R fb = (G.flip & GEMM_FLIP_B) == 0 ? R(1) : R(-1);
   auto store_a = [&]() {
 #pragma unroll
     for (int u = 0; u < EA; ++u) {
       const int k = AK ? qa + u : la, m = AK ? la : qa + u;
       sA_r[stage][k][m] = (R)ra[u].x;
-      sA_i[stage][k][m] = OPA == OP_N ? (R)ra[u].y : -(R)ra[u].y;
+      sA_i[stage][k][m] = fa * (R)ra[u].y;
     }
   };
   auto store_b = [&]() {
@@ -231,7 +236,7 @@ void gemm_kernel(const GemmArgs args) {
     for (int u = 0; u < EB; ++u) {
       const int k = BKC ? qb + u : lb, n = BKC ? lb : qb + u;
       sB_r[stage][k][n] = (R)rb[u].x;
-      sB_i[stage][k][n] = (R)rb[u].y;
+      sB_i[stage][k][n] = fb * (R)rb[u].y;
     }
   };
 
@@ -528,10 +533,13 @@ void gemm_tile_shape(int variant, int* bm, int* bn) {
 
 hipError_t launch_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int variant,
                        const GemmArgs& args, hipStream_t s) {
-  if (tacc == ACC_BF16X3)
+  if (tacc == ACC_BF16X3) {
+    for (int g = 0; g < args.ngroups; ++g)
+      if (args.g[g].flip) return hipErrorInvalidValue;
     return (ta == CT_F32 && tb == CT_F32 && tc == CT_F32 && args.epi == GEMM_EPI_NONE)
                ? launch_gemm_bf16x3(opa, opb, variant, args, s)
                : hipErrorInvalidValue;
+  }
   if (args.epi != GEMM_EPI_NONE) {   // gate operator in the epilogue
     for (int g = 0; g < args.ngroups; ++g)
       if (args.g[g].wl < 1 || args.g[g].wl > GEMM_EPI_WMAX || args.g[g].wr < 1 ||

@@ -509,6 +509,7 @@ int run_gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
       // the right epilogue's tiles hold columns (0, y) and (1, y) for bn / 2 values of y
       g.tiles_n = epi == GEMM_EPI_RIGHT ? (j.N / 2 + bn / 2 - 1) / (bn / 2) : (j.N + bn - 1) / bn;
       g.tiles_per_item = ((j.M + bm - 1) / bm) * g.tiles_n;
+      g.flip = j.flip;
       g.herm = j.herm && j.M == j.N && bm == bn && epi == GEMM_EPI_NONE && tacc != ACC_BF16X3;
       double part = 1.0;   // share of the product's tiles computed
       if (g.herm) {

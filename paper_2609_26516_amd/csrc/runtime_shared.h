@@ -44,6 +44,7 @@ struct GemmJob {
   // the product is Hermitian (M = N): computed on and below the diagonal
   // where the tile shape is square, and mirrored
   int herm = 0;
+  int flip = 0;   // GEMM_FLIP_*
 };
 struct QrJob {
   Operand f, q, ws, nrm2;

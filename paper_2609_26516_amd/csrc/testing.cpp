@@ -175,7 +175,8 @@ int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int
       return testing_fail(DCS_EINVAL, "bad op");
     const bool herm = (variant & 16) != 0;
     const bool far = (variant & 32) != 0;
-    variant &= ~48;
+    const int flip = (variant >> 6) & 3;
+    variant &= ~240;
     if (variant < 0 || variant >= GEMM_VARIANTS) return testing_fail(DCS_EINVAL, "bad tile shape");
     int bm = 64, bn = 64;
     gemm_tile_shape(variant, &bm, &bn);
@@ -214,6 +215,7 @@ int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int
     args.ngroups = 1;
     args.total_tiles = g.tiles_per_item * batch;
     args.far = far;
+    g.flip = flip;
     hipError_t e = launch_gemm(ta, tb, tc, tacc, opa, opb, variant, args, s);
     if (e == hipErrorInvalidValue) return testing_fail(DCS_EINVAL, "type/op combination not built");
     T_HIP(e);

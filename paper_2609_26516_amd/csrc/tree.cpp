@@ -542,50 +542,51 @@ struct Exec {
       if (std::find(shared.begin(), shared.end(), l) != shared.end()) shared_b.push_back(l);
     Ten A = A0, B = B0, tmpA, tmpB;
     bool pa = false, pb = false;
-    int opa = -1, opb = -1;
-    auto a_forms = [&](const Ten& a, const std::vector<int>& sh) {
-      std::vector<int> f;
-      if (a.legs == cat(fa, sh)) f.push_back(a.conj ? OP_J : OP_N);
-      if (a.conj && a.legs == cat(sh, fa)) f.push_back(OP_C);
-      return f;
+    int opa = -1, opb = -1, flip = 0;
+    const int acc = tc == CT_F64 ? CT_F64 : tacc;
+    // How a tensor's legs lie: 0 with its shared legs last, 1 with them first.
+    auto lies = [&](const Ten& t, const std::vector<int>& free_legs, const std::vector<int>& sh, int form) {
+      return t.legs == (form == 0 ? cat(free_legs, sh) : cat(sh, free_legs));
     };
-    auto b_forms = [&](const Ten& b, const std::vector<int>& sh) {
-      std::vector<int> f;
-      if (!b.conj && b.legs == cat(sh, fb)) f.push_back(OP_N);
-      if (!b.conj && b.legs == cat(fb, sh)) f.push_back(OP_T);
-      return f;
+    // A GEMM form for A (fa, sh) or (sh, fa) and B (sh, fb) or (fb, sh) in
+    // the storage types cta and ctb; conjugations that differ from the op's
+    // are flipped in the kernel.
+    auto choose = [&](int cta, int ctb, int form_a, int form_b, bool conj_a, bool conj_b) {
+      const int y = form_b == 1 ? OP_N : OP_T;
+      for (int x : {conj_a ? (int)OP_J : (int)OP_N, (int)OP_N, (int)OP_J, (int)OP_C}) {
+        if ((x == OP_C) != (form_a == 1) || !gemm_ok(cta, ctb, tc, x, y)) continue;
+        const int f = (conj_a != (x != OP_N) ? GEMM_FLIP_A : 0) | (conj_b ? GEMM_FLIP_B : 0);
+        if (f && acc == ACC_BF16X3) continue;
+        opa = x;
+        opb = y;
+        flip = f;
+        return true;
+      }
+      return false;
     };
     // 1: as stored (shared legs in A's order)
-    for (int x : a_forms(A, shared))
-      for (int y : b_forms(B, shared))
-        if (opa < 0 && gemm_ok(A.ct, B.ct, tc, x, y)) {
-          opa = x;
-          opb = y;
-        }
+    for (int x : {0, 1})
+      for (int y : {1, 0})
+        if (opa < 0 && lies(A, fa, shared, x) && lies(B, fb, shared, y))
+          choose(A.ct, B.ct, x, y, A.conj, B.conj);
     // 2: transpose B only
-    if (opa < 0) {
-      for (int x : a_forms(A, shared)) {
-        for (int ctb : {B.ct, (int)CT_F64}) {
-          if (opa < 0 && gemm_ok(A.ct, ctb, tc, x, OP_N)) {
-            TT_TRY(permute(B, cat(shared, fb), ctb, nullptr, &tmpB));
-            pb = true;
-            opa = x;
-            opb = OP_N;
-          }
+    for (int x : {0, 1}) {
+      if (opa >= 0 || !lies(A, fa, shared, x)) continue;
+      for (int ctb : {B.ct, (int)CT_F64}) {
+        if (opa < 0 && choose(A.ct, ctb, x, 1, A.conj, false)) {
+          TT_TRY(permute(B, cat(shared, fb), ctb, nullptr, &tmpB));
+          pb = true;
         }
       }
     }
     // 3: transpose A only (shared legs in B's order)
-    if (opa < 0) {
-      for (int y : b_forms(B, shared_b)) {
-        for (int cta : {A.ct, (int)CT_F64}) {
-          if (opa < 0 && gemm_ok(cta, B.ct, tc, OP_N, y)) {
-            TT_TRY(permute(A, cat(fa, shared_b), cta, nullptr, &tmpA));
-            pa = true;
-            shared = shared_b;
-            opa = OP_N;
-            opb = y;
-          }
+    for (int y : {1, 0}) {
+      if (opa >= 0 || !lies(B, fb, shared_b, y)) continue;
+      for (int cta : {A.ct, (int)CT_F64}) {
+        if (opa < 0 && choose(cta, B.ct, 0, y, false, B.conj)) {
+          TT_TRY(permute(A, cat(fa, shared_b), cta, nullptr, &tmpA));
+          pa = true;
+          shared = shared_b;
         }
       }
     }
@@ -635,7 +636,7 @@ struct Exec {
     j.ldb = (opb == OP_T) ? (int)K : (int)N;
     j.ldc = (int)N;
     j.batch = batch;
-    const int acc = tc == CT_F64 ? CT_F64 : tacc;
+    j.flip = flip;
     // Split sum: a complex128 contraction with a single output tile per item
     // and a long sum (the top-level inner products of the measurement) would
     // run as one workgroup per item; its sum is cut into chunks computed side
