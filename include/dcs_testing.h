@@ -31,7 +31,8 @@ extern "C" {
  * exactly Hermitian when the product is Hermitian; plus 32 (32x32 tiles only)
  * for the form with 64-bit addresses, taken for operands whose rows are 2^21
  * elements apart or more; plus 64 (128) to conjugate A (B) on top of its op,
- * not in the split-BF16 form. */
+ * not in the split-BF16 form; plus 256 parts for a sum split into that many
+ * parts (2 or more; none of them empty at 32-column granularity). */
 int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int N, int K,
                   int batch, int variant, const double *A, const double *B, double *C,
                   void *stream);

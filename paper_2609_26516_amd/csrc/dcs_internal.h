@@ -45,6 +45,11 @@ struct GemmGroup {
   // GEMM_FLIP_*: that operand is conjugated on top of its op (not in the
   // split-BF16 form)
   int flip;
+  // Split sum (parts > 1, no epilogue, not Hermitian, not in the split-BF16
+  // form): tiles_per_item counts the tiles of all parts; part q takes k in
+  // [q kc, (q + 1) kc), kc a multiple of 32, and writes its product at
+  // C + q M N (ldc = N), to be added by launch_ksum.
+  int parts, kc;
 };
 enum { GEMM_FLIP_A = 1, GEMM_FLIP_B = 2 };
 
@@ -260,13 +265,13 @@ hipError_t launch_permute(int ct_in, int ct_out, const PermuteArgs& a, hipStream
 // out_len is too small.
 bool permute_tile_plan(const PermuteArgs& a, int esize, int* out, int out_len);
 
-// Sum of the split-K partial products of a contraction (complex128):
+// Sum of the split-K partial products of a contraction (storage type ct):
 // out[item][e] = sum_{s < parts} part[item][s * mn + e] for e < mn, the
-// parts added in order s = 0, 1, ...
+// parts added in order s = 0, 1, ... in FP64
 struct KsumArgs {
   Operand part, out;
   const int* ids;
-  int parts, mn, batch, pad_;
+  int parts, mn, batch, ct;
 };
 hipError_t launch_ksum(const KsumArgs& a, hipStream_t s);
 

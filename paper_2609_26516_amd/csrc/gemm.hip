@@ -152,7 +152,13 @@ void gemm_kernel(const GemmArgs args) {
   const GemmGroup& G = args.g[gi];
   const int local = tile - G.tile_begin;
   const int item = local / G.tiles_per_item;
-  const int t = local - item * G.tiles_per_item;
+  int t = local - item * G.tiles_per_item;
+  int part = 0;
+  if (EPI == GEMM_EPI_NONE && G.parts > 1) {   // uniform
+    const int per = G.tiles_per_item / G.parts;
+    part = t / per;
+    t -= part * per;
+  }
   int tm = t / G.tiles_n, tn = t % G.tiles_n;
   if (EPI == GEMM_EPI_NONE && G.herm) {   // t = tm (tm + 1) / 2 + tn, tn <= tm
     tm = (int)((sqrtf(8.0f * t + 1.0f) - 1.0f) * 0.5f);
@@ -164,12 +170,20 @@ void gemm_kernel(const GemmArgs args) {
   // right epilogue: tile columns (t, y) for y in [n0, n0 + BN / 2), t = 0, 1
   const int n0 = tn * (EPI == GEMM_EPI_RIGHT ? BN / 2 : BN);
   const bool mirror = EPI == GEMM_EPI_NONE && G.herm && tn != tm;   // uniform
-  const int M = G.M, N = G.N, K = G.K;
+  const int M = G.M, N = G.N;
+  int K = G.K;
   const int lda = G.lda, ldb = G.ldb, ldc = G.ldc;
 
   const CA* __restrict__ A = reinterpret_cast<const CA*>(item_ptr(G.a, G.ids, item));
   const CB* __restrict__ B = reinterpret_cast<const CB*>(item_ptr(G.b, G.ids, item));
   CC* __restrict__ C = reinterpret_cast<CC*>(const_cast<char*>(item_ptr(G.c, G.ids, item)));
+  if (EPI == GEMM_EPI_NONE && G.parts > 1) {   // uniform
+    const int k0 = part * G.kc;
+    K = min(G.kc, K - k0);
+    A += (OPA == OP_N || OPA == OP_J) ? (long long)k0 : (long long)k0 * lda;
+    B += OPB == OP_T ? (long long)k0 : (long long)k0 * ldb;
+    C += (long long)part * M * N;
+  }
 
   const int tid = threadIdx.x;
   // staging: a thread takes EA (EB) consecutive elements of one line of the
@@ -221,8 +235,9 @@ void gemm_kernel(const GemmArgs args) {
                                         (long long)sizeof(CB)), vb, left, vec_b);
   };
   // signs of the imaginary parts: the op's conjugation and the group's flips
-  const R fa = (OPA == OP_N) == ((G.flip & GEMM_FLIP_A) == 0) ? R(1) : R(-1);
-  const R fb = (G.flip & GEMM_FLIP_B) == 0 ? R(1) : R(-1);
+  const int flip = EPI == GEMM_EPI_NONE ? G.flip : 0;
+  const R fa = (OPA == OP_N) == ((flip & GEMM_FLIP_A) == 0) ? R(1) : R(-1);
+  const R fb = (flip & GEMM_FLIP_B) == 0 ? R(1) : R(-1);
   auto store_a = [&]() {
 #pragma unroll
     for (int u = 0; u < EA; ++u) {

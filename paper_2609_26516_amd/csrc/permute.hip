@@ -404,20 +404,25 @@ hipError_t launch_tiled(const PermuteTileArgs& t, int ept, hipStream_t s) {
   return hipGetLastError();
 }
 
-// out[item][e] = sum_{s < parts} part[item][s * mn + e] (complex128), s in
-// ascending order.
+// out[item][e] = sum_{s < parts} part[item][s * mn + e], s in ascending order,
+// in FP64.
+template <int CT>
 __global__ __launch_bounds__(256) void ksum_kernel(const KsumArgs a) {
+  using T = typename St<CT>::T;
   const int item = blockIdx.y;
-  const double2* __restrict__ p = reinterpret_cast<const double2*>(item_ptr(a.part, a.ids, item));
-  double2* __restrict__ o = reinterpret_cast<double2*>(const_cast<char*>(item_ptr(a.out, a.ids, item)));
+  const T* __restrict__ p = reinterpret_cast<const T*>(item_ptr(a.part, a.ids, item));
+  T* __restrict__ o = reinterpret_cast<T*>(const_cast<char*>(item_ptr(a.out, a.ids, item)));
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < a.mn; e += gridDim.x * blockDim.x) {
     double re = 0, im = 0;
     for (int s = 0; s < a.parts; ++s) {
-      const double2 v = p[(long long)s * a.mn + e];
+      const T v = p[(long long)s * a.mn + e];
       re += v.x;
       im += v.y;
     }
-    o[e] = make_double2(re, im);
+    T w;
+    w.x = re;
+    w.y = im;
+    o[e] = w;
   }
 }
 
@@ -427,7 +432,10 @@ hipError_t launch_ksum(const KsumArgs& a, hipStream_t s) {
   if (a.batch <= 0 || a.mn <= 0) return hipSuccess;
   if (a.parts < 1 || a.batch > 65535) return hipErrorInvalidValue;
   const dim3 grid((unsigned)std::min(64, (a.mn + 255) / 256), (unsigned)a.batch), blk(256);
-  hipLaunchKernelGGL(ksum_kernel, grid, blk, 0, s, a);
+  if (a.ct == CT_F32)
+    hipLaunchKernelGGL(ksum_kernel<CT_F32>, grid, blk, 0, s, a);
+  else
+    hipLaunchKernelGGL(ksum_kernel<CT_F64>, grid, blk, 0, s, a);
   return hipGetLastError();
 }
 

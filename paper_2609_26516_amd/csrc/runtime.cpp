@@ -510,12 +510,15 @@ int run_gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
       g.tiles_n = epi == GEMM_EPI_RIGHT ? (j.N / 2 + bn / 2 - 1) / (bn / 2) : (j.N + bn - 1) / bn;
       g.tiles_per_item = ((j.M + bm - 1) / bm) * g.tiles_n;
       g.flip = j.flip;
+      g.parts = j.parts;
+      g.kc = j.kc;
       g.herm = j.herm && j.M == j.N && bm == bn && epi == GEMM_EPI_NONE && tacc != ACC_BF16X3;
       double part = 1.0;   // share of the product's tiles computed
       if (g.herm) {
         g.tiles_per_item = g.tiles_n * (g.tiles_n + 1) / 2;
         part = (double)g.tiles_per_item / ((double)g.tiles_n * g.tiles_n);
       }
+      if (j.parts > 1) g.tiles_per_item *= j.parts;
       g.tile_begin = tiles;
       tiles += g.tiles_per_item * j.batch;
       flops += 8.0 * j.M * j.N * (double)j.K * j.batch * part;
@@ -2599,7 +2602,7 @@ int permute(dcs_ctx* ctx, int ct_in, int ct_out, const PermuteArgs& a, hipStream
 }
 
 int ksum(dcs_ctx* ctx, const KsumArgs& a, hipStream_t s, int cls) {
-  const double bytes = 16.0 * a.mn * (a.parts + 1.0) * a.batch;
+  const double bytes = (double)csize_of(a.ct) * a.mn * (a.parts + 1.0) * a.batch;
   Timed t(ctx, s, cls, 2.0 * a.mn * a.parts * a.batch, bytes);
   DCS_HIP(launch_ksum(a, s));
   return DCS_OK;

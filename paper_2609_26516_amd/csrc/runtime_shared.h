@@ -45,6 +45,7 @@ struct GemmJob {
   // where the tile shape is square, and mirrored
   int herm = 0;
   int flip = 0;   // GEMM_FLIP_*
+  int parts = 1, kc = 0;   // split sum (see GemmGroup)
 };
 struct QrJob {
   Operand f, q, ws, nrm2;

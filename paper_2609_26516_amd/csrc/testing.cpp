@@ -176,8 +176,12 @@ int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int
     const bool herm = (variant & 16) != 0;
     const bool far = (variant & 32) != 0;
     const int flip = (variant >> 6) & 3;
-    variant &= ~240;
+    const int parts = std::max(1, variant >> 8);
+    variant &= 15;
     if (variant < 0 || variant >= GEMM_VARIANTS) return testing_fail(DCS_EINVAL, "bad tile shape");
+    const int kc = ((K + parts - 1) / parts + 31) / 32 * 32;
+    if (parts > 1 && (herm || tacc == ACC_BF16X3 || (long long)kc * (parts - 1) >= K))
+      return testing_fail(DCS_EINVAL, "no split sum of this many parts");
     int bm = 64, bn = 64;
     gemm_tile_shape(variant, &bm, &bn);
     if (herm && (M != N || bm != bn))
@@ -216,9 +220,29 @@ int dcs_test_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int M, int
     args.total_tiles = g.tiles_per_item * batch;
     args.far = far;
     g.flip = flip;
+    DevBuf dp;
+    if (parts > 1) {
+      T_HIP(hipMalloc(&dp.p, nc * csz(tc) * parts));
+      g.c = op_of(dp.p, (long long)M * N * csz(tc) * parts);
+      g.parts = parts;
+      g.kc = kc;
+      g.tiles_per_item *= parts;
+      args.total_tiles *= parts;
+    }
     hipError_t e = launch_gemm(ta, tb, tc, tacc, opa, opb, variant, args, s);
     if (e == hipErrorInvalidValue) return testing_fail(DCS_EINVAL, "type/op combination not built");
     T_HIP(e);
+    if (parts > 1) {
+      KsumArgs ka;
+      std::memset(&ka, 0, sizeof(ka));
+      ka.part = g.c;
+      ka.out = op_of(dc.p, (long long)M * N * csz(tc));
+      ka.parts = parts;
+      ka.mn = M * N;
+      ka.batch = batch;
+      ka.ct = tc;
+      T_HIP(launch_ksum(ka, s));
+    }
     std::vector<char> h(nc * csz(tc));
     T_HIP(hipMemcpyAsync(h.data(), dc.p, h.size(), hipMemcpyDeviceToHost, s));
     T_HIP(hipStreamSynchronize(s));

@@ -637,17 +637,26 @@ struct Exec {
     j.ldc = (int)N;
     j.batch = batch;
     j.flip = flip;
-    // Split sum: a complex128 contraction with a single output tile per item
-    // and a long sum (the top-level inner products of the measurement) would
-    // run as one workgroup per item; its sum is cut into chunks computed side
-    // by side into an executor buffer, then added chunk by chunk in order.
-    const long long item_tiles = ((M + 31) / 32) * ((N + 31) / 32) * (long long)batch;
-    long long parts = 1;
-    if (tc == CT_F64 && M * N <= 1024 && K >= 4096)
-      parts = std::max(1LL, std::min({K / 1024, 1024 / item_tiles, (long long)GEMM_MAX_GROUPS}));
-    // (without a free executor buffer the contraction runs unsplit)
+    // Split sum: a contraction with few output tiles and a long sum (inner
+    // products, and the environments of nodes with small upper bonds) would
+    // run as a few workgroups per item that wait for memory once per K step;
+    // its sum is cut into parts computed side by side into an executor
+    // buffer, then added in order.  Without a free buffer that holds the
+    // parts it runs unsplit.  Four 32 x 32 tiles or fewer, K = 512 or more,
+    // parts of 128 columns (four K steps) or more.  64 items, unsplit and
+    // split, in us: 8 x 8, K = 256 12.7 and 12.6, K = 512 20 and 14, K = 2048
+    // 64 and 22; 64 x 64 (four tiles), K = 512 21 and 23, K = 2048 67 and 57;
+    // 128 x 64 (eight), K = 512 29 and 34, K = 2048 90 and 102.
+    const long long item_tiles = ((M + 31) / 32) * ((N + 31) / 32);
+    long long parts = 1, kc = K;
+    if (!dry && item_tiles <= 4 && K >= 512 && acc != ACC_BF16X3) {
+      parts = std::min(K / 128, 64LL);
+      kc = ((K + parts - 1) / parts + 31) / 32 * 32;
+      parts = (K + kc - 1) / kc;
+      if ((size_t)(parts * M * N) * csize(tc) > tr->L.scratch) parts = 1;
+    }
     int pbuf = -1;
-    if (parts > 1 && !dry) {
+    if (parts > 1) {
       for (int i = 0; i < NBUF && pbuf < 0; ++i)
         if (!used[i]) {
           used[i] = true;
@@ -655,39 +664,28 @@ struct Exec {
         }
       if (pbuf < 0) parts = 1;
     }
-    if (parts > 1) {
-      const long long kc = (K + parts - 1) / parts;
-      parts = (K + kc - 1) / kc;
-      TT_TRY(fits(parts * M * N, CT_F64));
-      const Operand pop = pbuf >= 0 ? buf_op(pbuf) : rt::local(nullptr, 0);
-      std::vector<rt::GemmJob> jobs;
-      for (long long q = 0; q < parts; ++q) {
-        const long long k0 = q * kc;
-        rt::GemmJob jq = j;
-        jq.K = (int)std::min(kc, K - k0);
-        jq.a = offset_op(A.op, (size_t)(k0 * (opa == OP_C ? j.lda : 1)) * csize(A.ct));
-        jq.b = offset_op(B.op, (size_t)(k0 * (opb == OP_N ? j.ldb : 1)) * csize(B.ct));
-        jq.c = offset_op(pop, (size_t)(q * M * N) * csize(CT_F64));
-        jq.ldc = (int)N;
-        jobs.push_back(jq);
+    if (!dry) {
+      if (parts > 1) {
+        j.c = buf_op(pbuf);
+        j.parts = (int)parts;
+        j.kc = (int)kc;
       }
-      if (!dry) {
-        TT_TRY(rt::gemm(tr->ctx, A.ct, B.ct, tc, acc, opa, opb, jobs, s, cls));
-        KsumArgs ka;
-        std::memset(&ka, 0, sizeof(ka));
-        ka.part = pop;
-        ka.out = c.op;
-        ka.ids = ids;
-        ka.parts = (int)parts;
-        ka.mn = (int)(M * N);
-        ka.batch = batch;
-        TT_TRY(rt::ksum(tr->ctx, ka, s, cls));
-      }
+      TT_TRY(rt::gemm(tr->ctx, A.ct, B.ct, tc, acc, opa, opb, {j}, s, cls));
+    }
+    if (pbuf >= 0) {
+      KsumArgs ka;
+      std::memset(&ka, 0, sizeof(ka));
+      ka.part = j.c;
+      ka.out = c.op;
+      ka.ids = ids;
+      ka.parts = (int)parts;
+      ka.mn = (int)(M * N);
+      ka.batch = batch;
+      ka.ct = tc;
+      TT_TRY(rt::ksum(tr->ctx, ka, s, cls));
       Ten pt;
       pt.buf = pbuf;
       give(pt);
-    } else if (!dry) {
-      TT_TRY(rt::gemm(tr->ctx, A.ct, B.ct, tc, acc, opa, opb, {j}, s, cls));
     }
     if (pa) give(tmpA);
     if (pb) give(tmpB);
