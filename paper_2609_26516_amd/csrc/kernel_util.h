@@ -175,13 +175,6 @@ __device__ __forceinline__ void zero4(v4d_t& a) {
   a[3] = 0;
 }
 
-// Wave-level ordering of LDS traffic: what a wave has written, its own lanes
-// may read (the LDS serves one wave's accesses in order).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Wave-wide sum of a double without LDS round trips: four DPP steps (lane
 // xor 1, xor 2, half-row mirror, row mirror) leave every lane of a 16-lane
 // row with the same row sum, then the four row sums are read with readlane

@@ -665,7 +665,7 @@ __global__ __launch_bounds__(512, 1) void qrs_panel_kernel(const QrArgs args) {
 // reductions, then the panel's two one-wave recurrences.  Mean over the
 // launches of a round of 48 states at bonds up to 512: 51.0 us with the next
 // panel read back from memory, V read twice and the matrices' strips in
-// order, 40.7 now.
+// order, 44.7 now.
 __global__ __launch_bounds__(512, 1) void qrs_update_kernel(const QrArgs args, int p) {
   extern __shared__ __attribute__((aligned(16))) double2 qrs_dyn[];
   double2* sV = qrs_dyn;
@@ -874,17 +874,11 @@ __device__ __forceinline__ void qrt_reduce_store(double2* sWp, double2* dst, int
   }
 }
 
-// Sums the chunk parts src[0 .. nch), nch <= 8, in order into sWp.
+// Loads the chunk parts src[0 .. nch) into sWp as eight parts (zeros beyond
+// nch).
 __device__ __forceinline__ void qrt_load_parts(double2* sWp, const double2* src, int nch, int tid) {
-  if (tid < 256) {
-    double2 v[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] = c < nch ? src[c * 256 + tid] : make_double2(0.0, 0.0);
-    double2 s = v[0];
-#pragma unroll
-    for (int c = 1; c < 8; ++c) s = make_double2(s.x + v[c].x, s.y + v[c].y);
-    sWp[tid] = s;
-  }
+  for (int e = tid; e < 8 * 256; e += 512)
+    sWp[e] = (e >> 8) < nch ? src[e] : make_double2(0.0, 0.0);
 }
 
 __global__ __launch_bounds__(512, 1) void qrt_gram_kernel(const QrArgs args, int p) {

@@ -55,6 +55,13 @@ struct CAcc {
   __device__ __forceinline__ typename Path<CT>::R im(int r) const { return p3[r] - p1[r] - p2[r]; }
 };
 
+// Wave-level ordering of LDS traffic: what a wave has written, its own lanes
+// may read (the LDS serves one wave's accesses in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Workgroup barrier for LDS traffic alone: global stores stay in flight.
 __device__ __forceinline__ void lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
