@@ -254,7 +254,7 @@ __global__ __launch_bounds__(CNT) void chain_kernel(const ChainArgs A) {
   auto site_put = [&]() {
     aw.put(sW);
     if constexpr (ALL) ak.put(sK);
-    lds_sync();
+    __syncthreads();
   };
 
   // stage A of site j into X[(g, s)][(o, n)], with `ahead` on the way to LDS
@@ -294,8 +294,10 @@ __global__ __launch_bounds__(CNT) void chain_kernel(const ChainArgs A) {
         sE[0].y = 0;
       }
     }
-    // (sW and sK are free since stage A)
-    site_put();   // X and the scratch are free from here; E is in flight to memory
+    // (sW and sK are free since stage A.)  The barrier at its end orders global
+    // memory too: the next visit's waves read E as the other waves stored it.
+    // X and the scratch are free from here.
+    site_put();
   };
   // the visit after (t, j): false after the last one
   auto advance = [&](int t, int j, int& tn, int& jn) -> bool {
@@ -339,7 +341,7 @@ __global__ __launch_bounds__(CNT) void chain_kernel(const ChainArgs A) {
     ab.load(reinterpret_cast<const T*>(init + o_site(j)), dl * 2 * dr);
     stage_x(j, true);
     ab.put(sF);
-    __syncthreads();   // also: the stores of the last stage D have landed
+    __syncthreads();   // X may lie in global memory
     stage_d(dl, z, 2 * dr, j, j - 1, j > 1 || goes_left(1, 0), [&](int h, int k) {
       T v = sF[h * 2 * dr + (k & 1) * dr + (k >> 1)];   // k = (c, s): conj(B[h][s][c])
       v.y = -v.y;
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(CNT) void chain_kernel(const ChainArgs A) {
     if constexpr (ALL) ae.load(Eg, nh * z);
     stage_x(j, left);
     if constexpr (ALL) ae.put(sEa);
-    __syncthreads();   // also: the stores of the last stage D have landed
+    __syncthreads();   // X may lie in global memory
     auto put_f = [&](int r, int h, R re, R im) {   // rows (g, s); moving left (s, g), conjugated
       T v;
       v.x = re;
