@@ -56,22 +56,39 @@ struct QrSmem {
 // zlarfg: tau and inv = 1 / (alpha - beta), so v = [1; x inv]; the identity
 // (tau = inv = 0) where x has no non-zero entry (`some` false) and alpha is real,
 // or the squared norm n2 is below 1e-200 (the caller has scaled what is not zero).
+// I - tau v v^H is unitary to the accuracy of |(alpha, x)| and of the quotients,
+// so each ends in a residual correction (Markstein's iterations: nrm ->
+// sqrt(n2), h -> 1 / (2 sqrt(n2)), the residuals exact by FMA), and Re tau = 1 -
+// Re alpha / beta is rounded once.  The norms |q|^2 of random 32 x 16 columns
+// are 2.5e-16 from 1 (rms; LAPACK's 2.6e-16, the blocked kernel's 2.7e-16);
+// with plain Newton steps they were 3.2e-16 off, one-sided where the norm is a
+// round number: F of the 13-qubit GHZ circuit 3.0e-14 from its value, 3.6e-15
+// now.  The corrections cost nothing that shows in a step's time.
 __device__ __forceinline__ void reflector(double ar, double ai, double xn, double n2, bool some,
                                           double2& tau, double2& inv) {
-  double rs = __builtin_amdgcn_rsq(n2);   // 1 / |(alpha, x)|, two Newton steps
-  const double h = 0.5 * n2;
-  rs = rs * fma(-h * rs, rs, 1.5);
-  rs = rs * fma(-h * rs, rs, 1.5);
-  const double nrm = n2 * rs;
+  double rs = __builtin_amdgcn_rsq(n2);
+  double nrm = n2 * rs, h = 0.5 * rs;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double r = fma(-nrm, h, 0.5);
+    nrm = fma(nrm, r, nrm);
+    h = fma(h, r, h);
+  }
+  nrm = fma(fma(-nrm, nrm, n2), h, nrm);
+  rs = h + h;
+  rs = fma(fma(-nrm, rs, 1.0), rs, rs);   // 1 / |(alpha, x)|
   const bool pos = ar >= 0.0;
   const double beta = pos ? -nrm : nrm, rb = pos ? -rs : rs;
   const double dx = ar - beta, den = fma(dx, dx, ai * ai);
   double rd = __builtin_amdgcn_rcp(den);
-  rd = rd * fma(-den, rd, 2.0);
-  rd = rd * fma(-den, rd, 2.0);
+  rd = fma(fma(-den, rd, 1.0), rd, rd);
+  rd = fma(fma(-den, rd, 1.0), rd, rd);
   const bool id = !(n2 >= 1e-200 && (some || xn != 0.0 || ai != 0.0));
-  tau = make_double2(id ? 0.0 : (beta - ar) * rb, id ? 0.0 : -ai * rb);
-  inv = make_double2(id ? 0.0 : dx * rd, id ? 0.0 : -ai * rd);
+  double ix = dx * rd, iy = -ai * rd;
+  ix = fma(fma(-ix, den, dx), rd, ix);
+  iy = fma(fma(-iy, den, -ai), rd, iy);
+  tau = make_double2(id ? 0.0 : fma(-ar, rb, 1.0), id ? 0.0 : -ai * rb);
+  inv = make_double2(id ? 0.0 : ix, id ? 0.0 : iy);
 }
 // Whether column k needs the slow look: its squared norm leaves [1e-200,
 // 1e200], or |x|^2 is zero and alpha real (x may still hold tiny entries).
