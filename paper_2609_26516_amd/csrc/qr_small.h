@@ -101,10 +101,10 @@ __device__ __forceinline__ bool odd_column(double ai, double xn, double n2) {
   return e < 1023 - 664 || e > 1023 + 664 || (xn == 0.0 && ai == 0.0);
 }
 __device__ __forceinline__ bool in_range(double n2) { return n2 >= 1e-200 && n2 <= 1e200; }
-// Power of two that brings the largest entry ma near 1; 0 for a zero column
-// (below 1e-280).
+// Power of two (a normal number) that brings the largest entry ma near 1; 0 for a
+// zero column (below 1e-280), 1 where it is infinite (Q comes out as NaN).
 __device__ __forceinline__ double column_scale(double ma) {
-  return ma < 1e-280 ? 0.0 : ma < 1e300 ? ldexp(1.0, -ilogb(ma)) : 1.0;
+  return ma < 1e-280 ? 0.0 : ma <= 1.7976931348623157e308 ? ldexp(1.0, -ilogb(ma)) : 1.0;
 }
 
 // The columns of a block are taken in groups of four; between groups the

@@ -1,5 +1,6 @@
-"""Accuracy of the one-launch QR (kernel variant 8): the columns of Q have norm
-1 as closely as LAPACK's Householder columns."""
+"""Accuracy and range of the one-launch QR (kernel variant 8): the columns of Q
+have norm 1 as closely as LAPACK's Householder columns, and columns up to the
+largest finite numbers give LAPACK's Q."""
 import numpy as np
 import pytest
 
@@ -46,3 +47,25 @@ def test_column_norms(capi, m, n):
         ref.append(_norm_errors(np.linalg.qr(f)[0]))
     rms = [float(np.sqrt(np.mean(np.concatenate(e) ** 2))) for e in (ours, ref)]
     assert rms[0] <= 1.16 * rms[1]
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("m,n", [(2, 1), (16, 8), (32, 16), (64, 32), (96, 48)])
+def test_huge_columns(capi, m, n, mode):
+    """Entries up to 1e305, whose squares are infinite.  Scaling a column by a
+    power of two leaves Q as it is, so the reference is LAPACK's Q of the
+    unscaled matrix; bounds as for the scaled columns of test_gpu_qr_mid.  A
+    last column below 1e-280 counts as zero: its column of Q is only
+    orthonormal to the others."""
+    rng = np.random.default_rng([m, n, 1])
+    f = _rand(rng, m, n)
+    ref, _ = np.linalg.qr(f)
+    e = np.zeros(n, int)
+    e[0] = 1013               # 2^1013 = 8.8e304
+    if n > 2:
+        e[n // 2], e[n - 1] = 999, -999
+    q = _q(capi, f * np.ldexp(1.0, e), mode)
+    assert np.all(np.isfinite(q))
+    np.testing.assert_allclose(q.conj().T @ q, np.eye(n), atol=1e-12)
+    k = n - 1 if n > 2 else n
+    assert np.max(np.abs(q - ref)[:, :k]) < 1e-9
