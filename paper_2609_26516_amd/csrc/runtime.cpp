@@ -631,7 +631,12 @@ int run_qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& all, h
   // against 4.31 ms for 512, at bond 64 1.82 against 2.41 ms for one and 4.26
   // against 5.22 ms for 512.  Its larger matrices fill a CU's LDS, so many of
   // them are left to the blocked kernel, which runs four to a CU (1024 of 128 x
-  // 64: 0.24 against 0.59 ms; of 90 x 45 the one launch is still ahead).
+  // 64: 0.24 against 0.59 ms; of 90 x 45 the one launch is still ahead).  The
+  // rule looks at the call, not at each matrix: a large batch of both kinds
+  // sent by size goes in one launch more (16 qubits, one sweep, complex64: 600
+  // branches of bond 16 with 50 of bond 64 5.8 instead of 6.1 ms, but 600 of bond
+  // 32 with 100 of 64 7.2 instead of 6.9, 300 of 40 with 600 of 64 11.2 instead of
+  // 10.7).
   const bool mid = !spread && (items <= 512 || m_big <= 96);
   for (int path : {0, 4, 3, 1, 2}) {
     std::vector<QrJob> jobs;
@@ -1446,24 +1451,38 @@ struct ChainSize {
 
 // Whether one launch carries the whole step (launch_chain), one workgroup per
 // branch.  Up to bond dimension 16 that beats the chain of launches at every
-// batch (16 qubits, two sweeps, complex128: 0.71 against 1.57 ms for one branch,
-// 1.95 against 4.53 ms for 1024; operator bond 16: 1.20 against 2.59 ms).  Up to
-// 32 a visit is enough work to gain from several CUs, so it pays only while the
-// branches leave CUs idle and the operators are narrow (1.98 against 2.15 ms for
-// one branch, 2.06 against 2.67 ms for 64, but 4.30 against 3.91 ms for 300, and
-// 3.85 against 3.25 ms for one with operator bond 16).
+// batch (16 qubits, two sweeps, against the same step as launches: complex128
+// 0.71 and 1.24 ms for one branch, 1.87 and 12.1 ms for 1024, at operator bond 16
+// 2.04 and 3.90 ms for one; complex64 0.62 and 1.17, 1.60 and 7.06, 1.71 and 3.58).
+// Up to 32 a visit is enough work to gain from several CUs, so it pays only
+// while the branches leave CUs idle and the operators are narrow (300 branches
+// 4.30 against 3.91 ms, operator bond 16 3.85 against 3.25 ms for one).
+// A site between bonds past 24 costs the one workgroup a step more (another row
+// of 16 x 16 tiles) and the launches hardly anything, so under an operator of
+// two layers (4 x 4 bonds; between 4 and 1, one layer, the one launch stays
+// ahead) a step of many such sites takes more branches to pay: at bond 32, one
+// launch against launches, complex128 12 qubits (two such sites) 1.02 and 1.09 ms
+// for one branch; 16 qubits (six) 1.99 and 1.78 for one, 2.0 and 2.04 for 32; 24
+// qubits (14) 3.91 and 3.20 for one, 3.99 and 3.63 for 32, 4.03 and 4.10 for 64.
+// complex64, whose products are cheaper beside the same FP64 QR, turns later: 24
+// qubits 3.25 and 3.03 for one, 3.30 and 3.16 for 16, even at 32.
 bool chain_takes(const dcs_state* st, const std::vector<Group>& groups, int branches) {
   if (st->precision == DCS_BF16X3) return false;
-  int dmax = 0, wmax = 0;
+  int dmax = 0, wmax = 0, wide = 0;
   for (const Group& g : groups) {
     if (g.warm) return false;
+    auto d = [&](int b) { return std::max(g.Db[b], g.Kb[b]); };
+    int sites = 0;
     for (int b = 0; b <= st->L.n; ++b) {
-      dmax = std::max(dmax, std::max(g.Db[b], g.Kb[b]));
+      dmax = std::max(dmax, d(b));
       wmax = std::max(wmax, g.w[b]);
+      if (b > 0) sites += d(b - 1) > 24 && d(b) > 24 && g.w[b - 1] * g.w[b] > 4;
     }
+    wide = std::max(wide, sites);
   }
   if (dmax <= 16) return wmax <= CHAIN_MAX_W;
-  return dmax <= CHAIN_MAX_D && wmax <= 4 && branches <= 256;
+  if (dmax > CHAIN_MAX_D || wmax > 4 || branches > 256) return false;
+  return branches >= (st->L.ct == CT_F32 ? 3 * (wide - 10) : wide > 3 ? 4 * wide : 0);
 }
 
 // Uploads what launch_chain reads: the table of the branches, in group order,
