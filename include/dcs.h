@@ -121,7 +121,9 @@ int dcs_ctx_set_graphs(dcs_ctx *ctx, int enabled);
  * (off by default).  Classes (DCS_TIMING_CLASSES of them): 0-3 the
  * contraction GEMMs of the compression step by operand form (0 A B, 1 A B^T,
  * 2 A^H B, 3 conj(A) B^T), 4 gate-operator application, 5 QR/LQ gauge shift,
- * 6 measurement contractions, 7 other.  dcs_ctx_timing returns, per class,
+ * 6 measurement contractions, 7 other, among them the compression steps of
+ * small branches that run in one launch (the flops of their contractions,
+ * operators and QRs together).  dcs_ctx_timing returns, per class,
  * the number of launches, their summed duration in ms, and the algorithmic
  * flops and operand bytes (unpadded shapes) of those launches. */
 #define DCS_TIMING_CLASSES 8

@@ -1442,12 +1442,32 @@ struct Group {
   bool warm = false;   // starting guess built from the ket (every ket bond <= the bra's)
 };
 
-// Largest bonds and intermediate of a compression step that one launch takes
-// (launch_chain), its algorithmic flops and operand bytes.
-struct ChainSize {
-  ChainDims d = {};
-  double flops = 0, bytes = 0;
-};
+// Algorithmic flops of a compression step, as its launches count them when it
+// runs as many: the starting guess's environments, then the visits (the last
+// one normalises instead of the QR and makes no environment).
+double step_flops(const std::vector<Group>& groups, const std::vector<int>& visits) {
+  double total = 0;
+  for (const Group& g : groups) {
+    // site j moving right (left): environment behind a, ahead h; ket bonds and
+    // operator bonds alike
+    auto site = [&](int j, bool left, bool f, bool qr, bool env) {
+      const int b = left ? j + 1 : j, c = left ? j : j + 1;
+      const double a = g.Db[b], h = g.Db[c], kb = g.Kb[b], kc = g.Kb[c], wb = g.w[b], wc = g.w[c];
+      const double m = 2 * a;
+      return 8.0 * (a * wb * kb * 2 * kc + a * kc * 4 * wb * wc +
+                    ((f ? 1.0 : 0.0) + (env ? 1.0 : 0.0)) * m * h * wc * kc +
+                    (qr ? 2.0 * m * h * h - 2.0 * h * h * h / 3.0 : 0.0));
+    };
+    double f = 0;
+    for (size_t j = 1; j + 1 < g.Db.size(); ++j) f += site((int)j, true, false, false, true);
+    for (size_t v = 0; v < visits.size(); ++v) {
+      const bool last = v + 1 == visits.size();
+      f += site(visits[v], !last && visits[v + 1] < visits[v], true, !last, !last);
+    }
+    total += f * (double)g.members.size();
+  }
+  return total;
+}
 
 // Whether one launch carries the whole step (launch_chain), one workgroup per
 // branch.  Up to bond dimension 16 that beats the chain of launches at every
@@ -1489,7 +1509,7 @@ bool chain_takes(const dcs_state* st, const std::vector<Group>& groups, int bran
 // and behind it the gate operators (one copy per distinct chunk).
 int chain_upload(dcs_state* st, const std::vector<Group>& groups, const int* ids,
                  const dcs_chunk* const* chunks, int n, int sweeps, double* nrm, hipStream_t s,
-                 ChainArgs* ca, ChainSize* sz) {
+                 ChainArgs* ca, ChainDims* dims, double* io_bytes) {
   *ca = {};
   const Layout& L = st->L;
   const int nq = L.n;
@@ -1519,21 +1539,17 @@ int chain_upload(dcs_state* st, const std::vector<Group>& groups, const int* ids
   for (const Group& g : groups) {
     const double k = (double)g.members.size();
     for (int j = 0; j < nq; ++j) {
-      const double f = 2.0 * g.w[j] * g.w[j + 1];
       const size_t xr = (size_t)2 * g.Db[j] * g.w[j + 1] * g.Kb[j + 1];
       const size_t xl = (size_t)2 * g.Db[j + 1] * g.w[j] * g.Kb[j];
-      ChainDims& d = sz->d;
+      ChainDims& d = *dims;
       d.x_elems = std::max(d.x_elems, std::max(xr, xl));
       d.d_max = std::max(d.d_max, std::max(g.Db[j], g.Db[j + 1]));
       d.w_max = std::max(d.w_max, std::max(g.w[j], g.w[j + 1]));
       d.op_elems = std::max(d.op_elems, 4 * g.w[j] * g.w[j + 1]);
       d.e_elems = std::max(d.e_elems, (size_t)g.Db[j] * g.w[j] * g.Kb[j]);
       d.k_elems = std::max(d.k_elems, (size_t)2 * g.Kb[j] * g.Kb[j + 1]);
-      // one environment and `sweeps` visits of the site
-      sz->flops += 8.0 * k * (sweeps + 1) *
-                   (2.0 * g.Db[j] * g.Kb[j + 1] * (g.w[j] * (double)g.Kb[j] + f) +
-                    2.0 * g.Db[j] * (double)g.Db[j + 1] * g.w[j + 1] * g.Kb[j + 1] * 2.0);
-      sz->bytes += k * L.cs * 2.0 * ((double)g.Kb[j] * g.Kb[j + 1] + (double)g.Db[j] * g.Db[j + 1]);
+      // the ket's sites in, the new ones out
+      *io_bytes += k * L.cs * 2.0 * ((double)g.Kb[j] * g.Kb[j + 1] + (double)g.Db[j] * g.Db[j + 1]);
     }
     for (int i : g.members) {
       *tab++ = ids[i];
@@ -1632,8 +1648,10 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
     std::vector<int> ids_host;
     double* nrm_dev = reinterpret_cast<double*>(st->base + L.o_out);
     ChainArgs ca;
-    ChainSize csz;
-    if (chain) DCS_TRY(chain_upload(st, groups, ids, chunks, n, n_sweeps, nrm_dev, s, &ca, &csz));
+    ChainDims cd = {};
+    double chain_bytes = 0;
+    if (chain)
+      DCS_TRY(chain_upload(st, groups, ids, chunks, n, n_sweeps, nrm_dev, s, &ca, &cd, &chain_bytes));
     const size_t mpo_host_bytes = chain ? 0 : L.mpo_stride * (size_t)n;
     st->host_stage.resize(std::max(st->host_stage.size(), mpo_host_bytes));
     char* mh = st->host_stage.data();
@@ -1871,8 +1889,8 @@ int dcs_compress_step(dcs_state* st, int n, const int* ids, const dcs_chunk* con
     }
     auto enqueue = [&]() -> int {
       if (chain) {
-        Timed t(st->ctx, s, CLS_OTHER, csz.flops, csz.bytes);
-        DCS_HIP(launch_chain(ct, ca, n, csz.d, s));
+        Timed t(st->ctx, s, CLS_OTHER, step_flops(groups, visits), chain_bytes);
+        DCS_HIP(launch_chain(ct, ca, n, cd, s));
         return DCS_OK;
       }
       DCS_TRY(warm_bra());
