@@ -228,13 +228,18 @@ def run_gpu_multipath(prec: str, steps: int, warmup: int, timing: bool, workload
 
 def roofline(stats, prec, counters=False, names=None):
     """counters: the HBM counters in TRAFFIC were taken on this workload;
-    names: kernel names of the classes where they differ from KERNEL_NAMES."""
+    names: kernel names of the classes where they differ from KERNEL_NAMES.
+
+    Without contraction launches every compression step ran in one launch
+    (small branches), which is timed as "other"."""
     launches, ms, flops, byts = stats
     dom = int(np.argmax(ms))
+    one_launch = sum(launches[:4]) == 0
     avg_ms = ms[dom] / max(1, launches[dom])
     per_launch_flops = flops[dom] / max(1, launches[dom])
     per_launch_bytes = byts[dom] / max(1, launches[dom])
-    if CLASSES[dom].startswith("gemm") or CLASSES[dom] == "measure":
+    if CLASSES[dom].startswith("gemm") or CLASSES[dom] == "measure" or (
+            one_launch and CLASSES[dom] == "other"):
         peak, _ = PEAK[prec]
         ach = per_launch_flops / (avg_ms * 1e-3) / 1e12
         rl = {"bound": "mfma", "achieved": round(ach, 3), "peak": peak, "unit": "TFLOP/s",
@@ -251,15 +256,17 @@ def roofline(stats, prec, counters=False, names=None):
     if tr is not None:
         rl["traffic"] = round(tr)
         rl["traffic_over_algorithmic"] = round(tr / max(1.0, per_launch_bytes), 2)
-    rl["kernel"] = {**KERNEL_NAMES, **(names or {})}.get(CLASSES[dom], CLASSES[dom])
+    rl["kernel"] = {**KERNEL_NAMES, **({"other": "chain_kernel"} if one_launch else {}),
+                    **(names or {})}.get(CLASSES[dom], CLASSES[dom])
     rl["avg_launch_ms"] = round(avg_ms, 5)
     rl["launches"] = int(launches[dom])
     rl["time_share"] = round(ms[dom] / max(1e-12, sum(ms)), 4)
     rl["classes_ms"] = {c: round(v, 2) for c, v in zip(CLASSES, ms)}
     tot_f = sum(flops[:4])
     tot_ms = sum(ms[:4])
-    rl["all_contraction_gemms"] = {"achieved_tflops": round(tot_f / (tot_ms * 1e-3) / 1e12, 3),
-                                   "frac": round(tot_f / (tot_ms * 1e-3) / 1e12 / PEAK[prec][0], 4)}
+    rl["all_contraction_gemms"] = None if one_launch else {
+        "achieved_tflops": round(tot_f / (tot_ms * 1e-3) / 1e12, 3),
+        "frac": round(tot_f / (tot_ms * 1e-3) / 1e12 / PEAK[prec][0], 4)}
     return rl
 
 
