@@ -2638,9 +2638,9 @@ int permute(dcs_ctx* ctx, int ct_in, int ct_out, const PermuteArgs& a, hipStream
   return DCS_OK;
 }
 
-int ksum(dcs_ctx* ctx, const KsumArgs& a, hipStream_t s, int cls) {
+int ksum(dcs_ctx* ctx, const KsumArgs& a, int opa, int opb, hipStream_t s, int cls) {
   const double bytes = (double)csize_of(a.ct) * a.mn * (a.parts + 1.0) * a.batch;
-  Timed t(ctx, s, cls, 2.0 * a.mn * a.parts * a.batch, bytes);
+  Timed t(ctx, s, cls < 0 ? gemm_class(opa, opb) : cls, 2.0 * a.mn * a.parts * a.batch, bytes);
   DCS_HIP(launch_ksum(a, s));
   return DCS_OK;
 }

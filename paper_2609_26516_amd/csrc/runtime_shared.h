@@ -53,15 +53,16 @@ struct QrJob {
   int m, n, mode, batch;
 };
 
-// Timing classes of dcs_ctx_set_timing; CLS_BY_FORM files a GEMM under the
-// class of its operand form (0-3).
+// Timing classes of dcs_ctx_set_timing; CLS_BY_FORM files a GEMM (and
+// the sum of its parts) under the class of its operand form (0-3).
 enum { CLS_BY_FORM = -1, CLS_QR = 5, CLS_MEAS = 6, CLS_OTHER = 7 };
 
 int gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
          const std::vector<GemmJob>& jobs, hipStream_t s, int cls);
 int qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& jobs, hipStream_t s);
 int permute(dcs_ctx* ctx, int ct_in, int ct_out, const PermuteArgs& a, hipStream_t s);
-int ksum(dcs_ctx* ctx, const KsumArgs& a, hipStream_t s, int cls);
+// opa, opb: forms of the product whose parts are added
+int ksum(dcs_ctx* ctx, const KsumArgs& a, int opa, int opb, hipStream_t s, int cls);
 // Resolves pending tile-shape trials (after the stream has been synchronised).
 void tune_sync(dcs_ctx* ctx);
 int ctx_device(const dcs_ctx* ctx);

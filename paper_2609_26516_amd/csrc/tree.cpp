@@ -682,7 +682,7 @@ struct Exec {
       ka.mn = (int)(M * N);
       ka.batch = batch;
       ka.ct = tc;
-      TT_TRY(rt::ksum(tr->ctx, ka, s, cls));
+      TT_TRY(rt::ksum(tr->ctx, ka, opa, opb, s, cls));
       Ten pt;
       pt.buf = pbuf;
       give(pt);
