@@ -642,15 +642,20 @@ struct Exec {
     // run as a few workgroups per item that wait for memory once per K step;
     // its sum is cut into parts computed side by side into an executor
     // buffer, then added in order.  Without a free buffer that holds the
-    // parts it runs unsplit.  Four 32 x 32 tiles or fewer, K = 512 or more,
-    // parts of 128 columns (four K steps) or more.  64 items, unsplit and
-    // split, in us: 8 x 8, K = 256 12.7 and 12.6, K = 512 20 and 14, K = 2048
-    // 64 and 22; 64 x 64 (four tiles), K = 512 21 and 23, K = 2048 67 and 57;
-    // 128 x 64 (eight), K = 512 29 and 34, K = 2048 90 and 102.
-    const long long item_tiles = ((M + 31) / 32) * ((N + 31) / 32);
+    // parts it runs unsplit.  Four 32 x 32 tiles or fewer per item; parts of 128
+    // columns (four K steps) or more, as many as give the call 1024 workgroups
+    // (four to a CU; past that the parts only add writes); and no more tiles
+    // than the sum is long for, since a call that fills the chip by itself only
+    // loses.  complex64, unsplit and split with the sum of the parts, in us, 8 x 8
+    // tiles: 64 of them, K = 512 20 and 16, K = 2048 63 and 23; 128, K = 512 20 and
+    // 17; 256, K = 512 20.4 and 20.8 (32 x 32: 22 and 27), K = 1024 36 and 30; 512, K =
+    // 1024 47 and 48 (32 x 32: 52 and 65), K = 2048 87 and 85; 1024, K = 2048 147 and
+    // 153.  Per item 128 x 64 (eight tiles), 64 items: K = 512 29 and 34.
+    const long long item_tiles = ((M + 31) / 32) * ((N + 31) / 32), tiles = item_tiles * batch;
     long long parts = 1, kc = K;
-    if (!dry && item_tiles <= 4 && K >= 512 && acc != ACC_BF16X3) {
-      parts = std::min(K / 128, 64LL);
+    if (!dry && item_tiles <= 4 && K >= 512 && acc != ACC_BF16X3 &&
+        tiles <= (K < 1024 ? 128 : K < 2048 ? 256 : 512)) {
+      parts = std::min({K / 128, 1024 / tiles, 64LL});
       kc = ((K + parts - 1) / parts + 31) / 32 * 32;
       parts = (K + kc - 1) / kc;
       if ((size_t)(parts * M * N) * csize(tc) > tr->L.scratch) parts = 1;
