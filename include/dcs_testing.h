@@ -50,6 +50,9 @@ int dcs_test_gemm_gate(int ct, int dir, int M, int N, int K, int wl, int wr, int
                        const double *A, const double *B, const double *W, double *C,
                        void *stream);
 
+/* Columns per K step (8, 16 or 32) of a launch of 32x32 tiles (host only). */
+int dcs_test_gemm_step(int tacc, int M, int N, int K, int batch);
+
 /* Gate-operator application.  dir 0: in X1[d0][wl][2][d1] -> out
  * X2[d0][2][wr][d1]; dir 1: in Y1[d0][2][d1][wr] -> out Y2[wl][d0][2][d1];
  * w = W[wl][2][2][wr]. */

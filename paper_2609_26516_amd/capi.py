@@ -39,7 +39,7 @@ EXPORTED = [
     "dcs_tree_chunk_scratch", "dcs_tree_compress_step", "dcs_tree_measure_prob",
     "dcs_tree_collapse", "dcs_tree_export",
 ]
-EXPORTED_TESTING = ["dcs_test_gemm", "dcs_test_mpo", "dcs_test_qr", "dcs_test_copy",
+EXPORTED_TESTING = ["dcs_test_gemm", "dcs_test_gemm_step", "dcs_test_mpo", "dcs_test_qr", "dcs_test_copy",
                     "dcs_test_permute", "dcs_test_permute_dev", "dcs_test_gemm_gate",
                     "dcs_test_permute_plan"]
 
@@ -117,6 +117,7 @@ _SIGS = {
     "dcs_test_qr": (c_int, [c_int] * 6 + [_DP, _DP, _DP, _P]),
     "dcs_test_copy": (c_int, [_P, _P, ctypes.c_size_t, c_int, _P]),
     "dcs_test_permute": (c_int, [c_int] * 3 + [_IP, _IP] + [c_int] * 3 + [_DP, _DP, _P]),
+    "dcs_test_gemm_step": (c_int, [c_int] * 5),
     "dcs_test_gemm_gate": (c_int, [c_int] * 8 + [_DP, _DP, _DP, _DP, _P]),
     "dcs_test_permute_plan": (c_int, [c_int, _IP, _IP, c_int, _IP, c_int, _IP]),
     "dcs_test_permute_dev": (c_int, [c_int] * 3 + [_IP, _IP] + [c_int] * 3 + [_P, _P, c_int, _P]),
@@ -549,6 +550,13 @@ def dcs_test_permute_dev(ct_in, ct_out, dims, perm, src: int, dst: int, conj=Fal
     p = (ctypes.c_int * len(perm))(*perm)
     _check(_lib.dcs_test_permute_dev(ct_in, ct_out, len(dims), d, p, int(bool(conj)), batch,
                                      int(variant), src, dst, reps, stream))
+
+
+def dcs_test_gemm_step(tacc: int, m: int, n: int, k: int, batch: int) -> int:
+    step = _lib.dcs_test_gemm_step(tacc, m, n, k, batch)
+    if step < 0:
+        _check(step)
+    return step
 
 
 def dcs_test_gemm_gate(ct, direction, a, b, w, variant=0, stream=0) -> np.ndarray:

@@ -77,6 +77,9 @@ constexpr int GEMM_FAR_LD = 1 << 21;
 
 // Tile shapes of the GEMM kernel (output tile BM x BN per workgroup).
 enum GemmVariant { GEMM_64x64 = 0, GEMM_32x32 = 1, GEMM_128x64 = 2, GEMM_64x128 = 3, GEMM_128x128 = 4 };
+// Whether a launch of 32 x 32 tiles takes 32 (in FP64 16) columns per K step
+// instead of 8.
+bool gemm_long_steps(const GemmArgs& args, bool fp64);
 constexpr int GEMM_VARIANTS = 5;
 // Tile shapes available for an accumulation type: 128 x 128 only for FP32
 // accumulation (its FP64 accumulators would not fit the registers).

@@ -11,7 +11,7 @@
 // Tiling: one 256-thread workgroup (4 wave64 in a 2x2 grid) per BM x BN
 // output tile; each wave owns a (BM/2) x (BN/2) quadrant made of 16x16 MFMA
 // blocks with real and imaginary accumulators.  K advances in steps of 8
-// complex columns (32x32 tiles: 32, in FP64 16) through LDS held as split real / imaginary planes in
+// complex columns (few 32x32 tiles: 32, in FP64 16) through LDS held as split real / imaginary planes in
 // [k][m] order, so the 16 lanes of an MFMA operand row read consecutive
 // words.  The next K tile is fetched into registers while the current one is
 // multiplied and then stored into the second of two LDS stages, one barrier
@@ -74,15 +74,13 @@ struct Store<CT_F64> {
 
 // Complex columns per K step.  8 keeps two LDS stages of a 64x64 tile small
 // enough (17 KB in FP32, 35 KB in FP64) that registers, not LDS, bound the
-// workgroups per CU.  The 32x32 tile is chosen where few tiles exist or N is
-// small, and then waits for memory once per step: its step is 32 columns (16
-// in FP64), four (two) elements of each operand in flight per thread (two states at bond 45:
-// 8.2 us a launch with steps of 8, 7.1 now; the tree network's products, 64
-// branches: 25.1 ms a pass, 19.5 now).
+// workgroups per CU.  A launch of few 32x32 tiles waits for memory once per
+// step instead: LONG steps are 32 columns (16 in FP64), four (two) elements of
+// each operand in flight per thread (gemm_long_steps has the rule).
 // The MFMAs take k in ascending groups of 4, so results do not depend on it.
 constexpr int NT = 256, PAD = 4;
-template <typename R, int BM, int BN>
-constexpr int gemm_bk() { return BM * BN > 32 * 32 ? 8 : sizeof(R) == 4 ? 32 : 16; }
+template <typename R, bool LONG>
+constexpr int gemm_bk() { return !LONG ? 8 : sizeof(R) == 4 ? 32 : 16; }
 
 __device__ __forceinline__ int xcd_remap(int bid, int total) {
   const int q = total >> 3, r = total & 7;
@@ -101,9 +99,9 @@ __device__ __forceinline__ const char* item_ptr(const Operand& o, const int* ids
 // (FP32 64x64: 5; FP64 64x64, 96 accumulator registers: 3; FP64 128x64, 192:
 // one).  Without it the compiler spends registers freely (an FP64 64x64 tile
 // took more than 256 and ran one wave per SIMD).
-template <typename R, int BM, int BN>
+template <typename R, int BM, int BN, bool LONG>
 constexpr int gemm_min_blocks() {
-  const int lds = (int)((160 * 1024) / (2 * 2 * gemm_bk<R, BM, BN>() * ((BM + PAD) + (BN + PAD)) * sizeof(R)));
+  const int lds = (int)((160 * 1024) / (2 * 2 * gemm_bk<R, LONG>() * ((BM + PAD) + (BN + PAD)) * sizeof(R)));
   const int regs = sizeof(R) == 8 ? (BM * BN <= 32 * 32 ? 4 : BM * BN <= 64 * 64 ? 3 : 1)
                                    : (BM * BN <= 32 * 32 ? 4 : BM * BN <= 64 * 64 ? 5
                                                             : BM * BN <= 128 * 64 ? 3 : 2);
@@ -112,15 +110,16 @@ constexpr int gemm_min_blocks() {
 }
 
 // FAR: operand rows too far apart for a 32-bit window (args.far)
-template <int TA, int TB, int TC, typename R, int OPA, int OPB, int BM, int BN, int EPI, bool FAR>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(gemm_min_blocks<R, BM, BN>(), 8)))
+template <int TA, int TB, int TC, typename R, int OPA, int OPB, int BM, int BN, int EPI, bool FAR = false,
+          bool LONG = FAR>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(gemm_min_blocks<R, BM, BN, LONG>(), 8)))
 void gemm_kernel(const GemmArgs args) {
   static_assert(EPI != GEMM_EPI_RIGHT || OPB == OP_N, "the right epilogue maps B's columns");
   using CA = typename Store<TA>::T;
   using CB = typename Store<TB>::T;
   using CC = typename Store<TC>::T;
   using V = typename Mfma<R>::V;
-  constexpr int BK = gemm_bk<R, BM, BN>();
+  constexpr int BK = gemm_bk<R, LONG>();
   constexpr int TPK = NT / BK;       // threads per k row when a row is staged along m / n
   constexpr int EA = BM * BK / NT;   // A elements staged per thread
   constexpr int EB = BN * BK / NT;   // B elements staged per thread
@@ -494,23 +493,26 @@ hipError_t run(int variant, const GemmArgs& args, hipStream_t s) {
   const dim3 grid(args.total_tiles), blk(NT);
   switch (variant) {
     case GEMM_64x64:
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 64, EPI, false>), grid, blk, 0, s, args);
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 64, EPI>), grid, blk, 0, s, args);
       break;
     case GEMM_32x32:
       if (args.far)
         hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 32, 32, EPI, true>), grid, blk, 0, s, args);
+      else if (gemm_long_steps(args, sizeof(R) == 8))
+        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 32, 32, EPI, false, true>), grid, blk, 0, s,
+                           args);
       else
-        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 32, 32, EPI, false>), grid, blk, 0, s, args);
+        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 32, 32, EPI>), grid, blk, 0, s, args);
       break;
     case GEMM_128x64:
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 64, EPI, false>), grid, blk, 0, s, args);
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 64, EPI>), grid, blk, 0, s, args);
       break;
     case GEMM_64x128:
-      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 128, EPI, false>), grid, blk, 0, s, args);
+      hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 64, 128, EPI>), grid, blk, 0, s, args);
       break;
     case GEMM_128x128:
       if constexpr (sizeof(R) == 4) {
-        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 128, EPI, false>), grid, blk, 0, s, args);
+        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, R, OPA, OPB, 128, 128, EPI>), grid, blk, 0, s, args);
         break;
       }
       return hipErrorInvalidValue;
@@ -544,6 +546,30 @@ void gemm_tile_shape(int variant, int* bm, int* bn) {
       *bm = 64;
       *bn = 64;
   }
+}
+
+// Long steps pay while a launch leaves room on the CUs (two LDS stages of them
+// are 37 KB, four workgroups to a CU instead of eight) and the sums are not
+// mostly the last step's padding.  32x32 tiles, long against short steps in us:
+// complex64 288 tiles, K = 90 8.0 and 8.8; 16 tiles, K = 128 7.2 and 9.9; 240 tiles, K =
+// 40 (64 columns of long steps, 40 of short ones) 5.7 and 5.5; 600, K = 40 8.8 and
+// 7.3; 960, K = 180 18.7 and 19.9; 1200, K = 90 15.3 and 15.0; 3072, K = 66 26.9 and
+// 21.3; 7680, K = 40 46 and 30.  FP64 differs less.
+// The lines: 1024 tiles where the steps fit (5 % of padding), a tile per CU up
+// to a third of padding (a tenth in FP64).
+bool gemm_long_steps(const GemmArgs& args, bool fp64) {
+  const long long bk = fp64 ? 16 : 32;
+  double with_long = 0, with_short = 0;
+  for (int i = 0; i < args.ngroups; ++i) {
+    const GemmGroup& g = args.g[i];
+    const long long k = g.parts > 1 ? g.kc : g.K;
+    const double tiles = (double)g.tiles_per_item * g.batch;
+    with_long += tiles * ((k + bk - 1) / bk * bk);
+    with_short += tiles * ((k + 7) / 8 * 8);
+  }
+  return args.total_tiles <= (with_long <= 1.05 * with_short                       ? 1024
+                              : with_long <= (fp64 ? 1.1 : 1.35) * with_short ? 256
+                                                                                   : 0);
 }
 
 hipError_t launch_gemm(int ta, int tb, int tc, int tacc, int opa, int opb, int variant,

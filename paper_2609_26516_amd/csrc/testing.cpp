@@ -354,6 +354,23 @@ int dcs_test_qr(int ct_in, int ct_out, int m, int n, int mode, int use_lds, cons
   });
 }
 
+int dcs_test_gemm_step(int tacc, int M, int N, int K, int batch) {
+  if ((tacc != CT_F32 && tacc != CT_F64) || M < 1 || N < 1 || K < 1 || batch < 1)
+    return testing_fail(DCS_EINVAL, "bad GEMM step arguments");
+  GemmArgs args;
+  std::memset(&args, 0, sizeof(args));
+  GemmGroup& g = args.g[0];
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.batch = batch;
+  g.tiles_n = (N + 31) / 32;
+  g.tiles_per_item = ((M + 31) / 32) * g.tiles_n;
+  args.ngroups = 1;
+  args.total_tiles = g.tiles_per_item * batch;
+  return !gemm_long_steps(args, tacc == CT_F64) ? 8 : tacc == CT_F64 ? 16 : 32;
+}
+
 int dcs_test_gemm_gate(int ct, int dir, int M, int N, int K, int wl, int wr, int variant,
                        const double* A, const double* B, const double* W, double* C,
                        void* stream) {
