@@ -77,6 +77,11 @@ int dcs_test_mpo(int ct, int dir, int d0, int d1, int wl, int wr, const double *
 int dcs_test_qr(int ct_in, int ct_out, int m, int n, int mode, int variant, const double *F,
                 double *Q, double *nrm2_out, void *stream);
 
+/* Path that a call of `batch` QRs of one shape takes (host only): 0 the blocked
+ * kernel (variants 4 to 6), 1 the large-matrix path (3), 2 the unblocked kernel
+ * (0), 3 the spread path (7), 4 one launch (8). */
+int dcs_test_qr_path(int m, int n, int mode, int batch);
+
 /* Device-to-device copy of `bytes` (a multiple of 16; both pointers device
  * memory, 16-byte aligned) from src to dst, `reps` times, enqueued on the
  * stream without synchronisation: `bytes` read and `bytes` written per launch.

@@ -39,7 +39,8 @@ EXPORTED = [
     "dcs_tree_chunk_scratch", "dcs_tree_compress_step", "dcs_tree_measure_prob",
     "dcs_tree_collapse", "dcs_tree_export",
 ]
-EXPORTED_TESTING = ["dcs_test_gemm", "dcs_test_gemm_step", "dcs_test_mpo", "dcs_test_qr", "dcs_test_copy",
+EXPORTED_TESTING = ["dcs_test_gemm", "dcs_test_gemm_step", "dcs_test_mpo", "dcs_test_qr",
+                    "dcs_test_qr_path", "dcs_test_copy",
                     "dcs_test_permute", "dcs_test_permute_dev", "dcs_test_gemm_gate",
                     "dcs_test_permute_plan"]
 
@@ -118,6 +119,7 @@ _SIGS = {
     "dcs_test_copy": (c_int, [_P, _P, ctypes.c_size_t, c_int, _P]),
     "dcs_test_permute": (c_int, [c_int] * 3 + [_IP, _IP] + [c_int] * 3 + [_DP, _DP, _P]),
     "dcs_test_gemm_step": (c_int, [c_int] * 5),
+    "dcs_test_qr_path": (c_int, [c_int] * 4),
     "dcs_test_gemm_gate": (c_int, [c_int] * 8 + [_DP, _DP, _DP, _DP, _P]),
     "dcs_test_permute_plan": (c_int, [c_int, _IP, _IP, c_int, _IP, c_int, _IP]),
     "dcs_test_permute_dev": (c_int, [c_int] * 3 + [_IP, _IP] + [c_int] * 3 + [_P, _P, c_int, _P]),
@@ -521,6 +523,13 @@ def dcs_test_qr(ct_in, ct_out, m, n, mode, variant, f, stream=0):
     _check(_lib.dcs_test_qr(ct_in, ct_out, m, n, mode, int(variant),
                             _dp(f.view(np.float64)), _dp(q.view(np.float64)), _dp(nrm), stream))
     return q, float(nrm[0])
+
+
+def dcs_test_qr_path(m: int, n: int, mode: int, batch: int) -> int:
+    path = _lib.dcs_test_qr_path(m, n, mode, batch)
+    if path < 0:
+        _check(path)
+    return path
 
 
 def dcs_test_copy(src: int, dst: int, nbytes: int, reps: int = 1, stream: int = 0) -> None:

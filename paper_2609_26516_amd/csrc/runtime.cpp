@@ -598,7 +598,7 @@ using QrJob = rt::QrJob;
 // Path of a QR job: 0 blocked single-workgroup kernel, left-looking form
 // (m <= 512 or mode 2), 4 the one-launch form for small and medium matrices
 // when `mid`, 3 the spread path for the same matrices when `spread`
-// (see run_qr), 1 multi-kernel large-matrix path, 2 unblocked kernel (beyond
+// (see qr_forms), 1 multi-kernel large-matrix path, 2 unblocked kernel (beyond
 // both).
 int qr_path(const QrJob& j, bool spread, bool mid) {
   if (j.mode == 2) return 0;
@@ -607,7 +607,8 @@ int qr_path(const QrJob& j, bool spread, bool mid) {
   return j.m <= qr_large_max_rows() ? 1 : 2;
 }
 
-int run_qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& all, hipStream_t s) {
+// Forms that a call's QRs may take (qr_path).
+void qr_forms(const std::vector<QrJob>& all, bool* spread, bool* mid) {
   // A call with few matrices of up to 512 rows leaves most of the chip idle
   // under one workgroup per matrix; when its largest matrix is big enough for
   // that to matter (more than 128 rows, at least 64 columns) its QRs take the
@@ -624,20 +625,26 @@ int run_qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& all, h
       m_big = std::max(m_big, j.m);
       n_big = std::max(n_big, j.n);
     }
-  const bool spread = items <= qr_spread_max_items() && m_big > 128 && n_big >= 64;
+  *spread = items <= qr_spread_max_items() && m_big > 128 && n_big >= 64;
   // Matrices of up to 128 x 64 in one launch instead of a factorisation and a
   // Q launch (or one launch of the blocked kernel from 161 matrices on): a step
   // of 14 qubits at bond 45 takes 2.05 against 3.26 ms for 256 branches and 3.41
   // against 4.31 ms for 512, at bond 64 1.82 against 2.41 ms for one and 4.26
-  // against 5.22 ms for 512.  Its larger matrices fill a CU's LDS, so many of
-  // them are left to the blocked kernel, which runs four to a CU (1024 of 128 x
-  // 64: 0.24 against 0.59 ms; of 90 x 45 the one launch is still ahead).  The
+  // against 5.22 ms for 512.  Past 512 the blocked kernel with two waves per matrix
+  // hides more chains on a CU (16 qubits, one sweep, complex64, 1024 branches: bond
+  // 32 8.13 and 7.74 ms, bond 48 10.33 and 9.79, 2048 at bond 48 20.2 and 19.4; 1024
+  // matrices of 128 x 64 0.59 and 0.24 ms), but for matrices of at most 48 rows
+  // (2048 branches at bond 20 13.8 and 14.3; 700 at bond 24 5.20 and 5.22).  The
   // rule looks at the call, not at each matrix: a large batch of both kinds
-  // sent by size goes in one launch more (16 qubits, one sweep, complex64: 600
-  // branches of bond 16 with 50 of bond 64 5.8 instead of 6.1 ms, but 600 of bond
-  // 32 with 100 of 64 7.2 instead of 6.9, 300 of 40 with 600 of 64 11.2 instead of
-  // 10.7).
-  const bool mid = !spread && (items <= 512 || m_big <= 96);
+  // sent by size goes in one launch more (600 branches of bond 16 with 50 of bond 64
+  // 5.8 instead of 6.1 ms, but 600 of bond 32 with 100 of 64 7.2 instead of 6.9, 300
+  // of 40 with 600 of 64 11.2 instead of 10.7).
+  *mid = !*spread && (items <= 512 || m_big <= 48);
+}
+
+int run_qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& all, hipStream_t s) {
+  bool spread, mid;
+  qr_forms(all, &spread, &mid);
   for (int path : {0, 4, 3, 1, 2}) {
     std::vector<QrJob> jobs;
     for (const QrJob& j : all)
@@ -2629,6 +2636,17 @@ int gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
 
 int qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& jobs, hipStream_t s) {
   return run_qr(ctx, ct_in, ct_out, jobs, s);
+}
+
+int qr_path_of(int m, int n, int mode, int batch) {
+  QrJob j = {};
+  j.m = m;
+  j.n = n;
+  j.mode = mode;
+  j.batch = batch;
+  bool spread, mid;
+  qr_forms({j}, &spread, &mid);
+  return qr_path(j, spread, mid);
 }
 
 int permute(dcs_ctx* ctx, int ct_in, int ct_out, const PermuteArgs& a, hipStream_t s) {

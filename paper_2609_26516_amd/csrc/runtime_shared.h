@@ -60,6 +60,9 @@ enum { CLS_BY_FORM = -1, CLS_QR = 5, CLS_MEAS = 6, CLS_OTHER = 7 };
 int gemm(dcs_ctx* ctx, int ta, int tb, int tc, int tacc, int opa, int opb,
          const std::vector<GemmJob>& jobs, hipStream_t s, int cls);
 int qr(dcs_ctx* ctx, int ct_in, int ct_out, const std::vector<QrJob>& jobs, hipStream_t s);
+// Path that a call of `batch` QRs of one shape takes: 0 blocked kernel, 1 large
+// path, 2 unblocked, 3 spread path, 4 one launch.
+int qr_path_of(int m, int n, int mode, int batch);
 int permute(dcs_ctx* ctx, int ct_in, int ct_out, const PermuteArgs& a, hipStream_t s);
 // opa, opb: forms of the product whose parts are added
 int ksum(dcs_ctx* ctx, const KsumArgs& a, int opa, int opb, hipStream_t s, int cls);

@@ -10,6 +10,7 @@
 
 #include "dcs.h"
 #include "dcs_internal.h"
+#include "runtime_shared.h"
 #include "dcs_testing.h"
 
 using namespace dcs;
@@ -369,6 +370,12 @@ int dcs_test_gemm_step(int tacc, int M, int N, int K, int batch) {
   args.ngroups = 1;
   args.total_tiles = g.tiles_per_item * batch;
   return !gemm_long_steps(args, tacc == CT_F64) ? 8 : tacc == CT_F64 ? 16 : 32;
+}
+
+int dcs_test_qr_path(int m, int n, int mode, int batch) {
+  if (m < 1 || n < 1 || mode < 0 || mode > 2 || batch < 1)
+    return testing_fail(DCS_EINVAL, "bad QR path arguments");
+  return rt::qr_path_of(m, n, mode, batch);
 }
 
 int dcs_test_gemm_gate(int ct, int dir, int M, int N, int K, int wl, int wr, int variant,
