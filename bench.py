@@ -43,24 +43,42 @@ CLASSES = ["gemm_nn", "gemm_nt", "gemm_cn", "gemm_jt", "gate_operator", "qr", "m
 KERNEL_NAMES = {
     "gemm_nn": "gemm_kernel<0, 0, 0, float, 0, 0>", "gemm_nt": "gemm_kernel<0, 0, 0, float, 0, 1>",
     "gemm_cn": "gemm_kernel<0, 0, 0, float, 2, 0>", "gemm_jt": "gemm_kernel<0, 0, 0, float, 3, 1>",
-    "gate_operator": "mpo_right_kernel / mpo_left_kernel", "qr": "qr_left_kernel<0, 0, 512 | 256>",
+    "gate_operator": "mpo_right_kernel / mpo_left_kernel",
+    "qr": "qr_left_kernel<0, 0, 512 | 256> (up to 128 x 64: qr_mid_kernel, qr_small_kernel)",
 }
 
 
 TUNE = {"enabled": True, "save": None}
 
 
-# HBM bytes of the dominant kernel from two rocprofv3 --pmc passes (FETCH_SIZE,
-# then WRITE_SIZE, KiB per dispatch, averaged over the kernel's dispatches in
-# one default step), each scaled by what the counter reads for a plain copy
-# of known size.  Valid only for the kernel source they were taken on.
+# HBM bytes of the dominant class of launches from two rocprofv3 --pmc passes
+# (FETCH_SIZE, then WRITE_SIZE, KiB, summed over the class's kernels in the
+# default steps and divided by the class's launches), each scaled by what the
+# counter reads for a plain copy of known size.  Valid only for the kernel
+# sources and the choice among them (the part of the runtime between the marks)
+# that they were taken on.
 TRAFFIC = {
     "qr": {"src": ["paper_2609_26516_amd/csrc/kernels.hip", "paper_2609_26516_amd/csrc/qr_panel.h",
-                   "paper_2609_26516_amd/csrc/qr_cholpanel.h", "paper_2609_26516_amd/csrc/kernel_util.h"],
-           "sha256": "c83839423b301ba0c9187665c893ee8c5b6bb761681f887b94c1238a938f87da",
-           "fetch_kib": 2501359.8, "write_kib": 979570.9,
-           "fetch_factor": 1048576 / 524300.5, "write_factor": 1048576 / 1048576.3},
+                   "paper_2609_26516_amd/csrc/qr_cholpanel.h", "paper_2609_26516_amd/csrc/kernel_util.h",
+                   "paper_2609_26516_amd/csrc/qr_mid.hip", "paper_2609_26516_amd/csrc/qr_small.h",
+                   "paper_2609_26516_amd/csrc/wg_tile.h"],
+           "choice": ("paper_2609_26516_amd/csrc/runtime.cpp", "int qr_path(", "struct NormJob"),
+           "sha256": "6cf19198acdb1a98d495d2cfa8a44409a882079c822d5b21e1c15c4e6ef95bec",
+           "fetch_kib": 2492779.5, "write_kib": 1001060.9,
+           "fetch_factor": 1048576 / 524300.6, "write_factor": 1048576 / 1048576.0},
 }
+
+
+def traffic_sources(t):
+    """What a traffic figure was taken on, as bytes."""
+    text = b""
+    for src in t["src"]:
+        with open(os.path.join(ROOT, src), "rb") as f:
+            text += f.read()
+    path, first, last = t["choice"]
+    with open(os.path.join(ROOT, path)) as f:
+        code = f.read()
+    return text + code[code.index(first):code.index(last)].encode()
 
 
 def measured_traffic(cls):
@@ -68,12 +86,8 @@ def measured_traffic(cls):
     t = TRAFFIC.get(cls)
     if t is None:
         return None
-    h = hashlib.sha256()
-    for src in t["src"]:
-        with open(os.path.join(ROOT, src), "rb") as f:
-            h.update(f.read())
-    if h.hexdigest() != t["sha256"]:
-        return None       # kernel changed since the counters were taken
+    if hashlib.sha256(traffic_sources(t)).hexdigest() != t["sha256"]:
+        return None       # kernels or their choice changed since the counters were taken
     return (t["fetch_kib"] * t["fetch_factor"] + t["write_kib"] * t["write_factor"]) * 1024.0
 
 
