@@ -58,8 +58,9 @@ struct QrSmem {
 // or the squared norm n2 is below 1e-200 (the caller has scaled what is not zero).
 // I - tau v v^H is unitary to the accuracy of |(alpha, x)| and of the quotients,
 // so each ends in a residual correction (Markstein's iterations: nrm ->
-// sqrt(n2), h -> 1 / (2 sqrt(n2)), the residuals exact by FMA), and Re tau = 1 -
-// Re alpha / beta is rounded once.  The norms |q|^2 of random 32 x 16 columns
+// sqrt(n2), h -> 1 / (2 sqrt(n2)), the residuals exact by FMA; the estimates are
+// good to 2^-24, one step to 2^-47, the correction to the rounding), and Re tau =
+// 1 - Re alpha / beta is rounded once.  The norms |q|^2 of random 32 x 16 columns
 // are 2.5e-16 from 1 (rms; LAPACK's 2.6e-16, the blocked kernel's 2.7e-16);
 // with plain Newton steps they were 3.2e-16 off, one-sided where the norm is a
 // round number: F of the 13-qubit GHZ circuit 3.0e-14 from its value, 3.6e-15
@@ -68,12 +69,9 @@ __device__ __forceinline__ void reflector(double ar, double ai, double xn, doubl
                                           double2& tau, double2& inv) {
   double rs = __builtin_amdgcn_rsq(n2);
   double nrm = n2 * rs, h = 0.5 * rs;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const double r = fma(-nrm, h, 0.5);
-    nrm = fma(nrm, r, nrm);
-    h = fma(h, r, h);
-  }
+  const double r = fma(-nrm, h, 0.5);
+  nrm = fma(nrm, r, nrm);
+  h = fma(h, r, h);
   nrm = fma(fma(-nrm, nrm, n2), h, nrm);
   rs = h + h;
   rs = fma(fma(-nrm, rs, 1.0), rs, rs);   // 1 / |(alpha, x)|
@@ -81,7 +79,6 @@ __device__ __forceinline__ void reflector(double ar, double ai, double xn, doubl
   const double beta = pos ? -nrm : nrm, rb = pos ? -rs : rs;
   const double dx = ar - beta, den = fma(dx, dx, ai * ai);
   double rd = __builtin_amdgcn_rcp(den);
-  rd = fma(fma(-den, rd, 1.0), rd, rd);
   rd = fma(fma(-den, rd, 1.0), rd, rd);
   const bool id = !(n2 >= 1e-200 && (some || xn != 0.0 || ai != 0.0));
   double ix = dx * rd, iy = -ai * rd;
