@@ -63,8 +63,8 @@ TRAFFIC = {
                    "paper_2609_26516_amd/csrc/qr_mid.hip", "paper_2609_26516_amd/csrc/qr_small.h",
                    "paper_2609_26516_amd/csrc/wg_tile.h"],
            "choice": ("paper_2609_26516_amd/csrc/runtime.cpp", "int qr_path(", "struct NormJob"),
-           "sha256": "6cf19198acdb1a98d495d2cfa8a44409a882079c822d5b21e1c15c4e6ef95bec",
-           "fetch_kib": 2492779.5, "write_kib": 1001060.9,
+           "sha256": "b499703ee2bcc779fbf317bf9eac3d515376b10b02e0f3feb5e7d9888f03c549",
+           "fetch_kib": 2491561.4, "write_kib": 1005888.0,
            "fetch_factor": 1048576 / 524300.6, "write_factor": 1048576 / 1048576.0},
 }
 

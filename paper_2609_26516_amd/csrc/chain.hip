@@ -22,11 +22,11 @@
 // products per complex one); the QR is FP64 in every form.
 //
 // What bounds it is the chain of one workgroup: at bond 16 a visit takes about
-// 53 000 cycles, half of them in the QR (about 2000 per column, some 265
+// 53 000 cycles, three fifths of them in the QR (about 2000 per column, some 265
 // instructions on one wave), 9000 in stage A, 5000 each in B and D.  16 qubits,
-// bond 16, two sweeps, one complex128 branch: 0.71 ms, against 1.57 ms as a
+// bond 16, two sweeps, one complex128 branch: 0.71 ms, against 1.24 ms as a
 // sequence of launches (15 environments and 31 visits of 4 to 5 launches); 64
-// branches 0.74 against 1.93 ms; bond 4: 0.43 against 1.15 ms.
+// branches 0.73 against 1.70 ms; bond 4: 0.43 against 0.90 ms.
 #include "qr_small.h"
 
 namespace dcs {

@@ -663,7 +663,7 @@ __global__ __launch_bounds__(512, 1) void qrs_panel_kernel(const QrArgs args) {
 // workgroups take longest, so the matrices' first strips come first in the
 // grid.  A launch is bounded by this chain: the update's loads and two
 // reductions, then the panel's two one-wave recurrences.  Mean over the
-// launches of a round of 48 states at bonds up to 512: 51.0 us with the next
+// launches of a round of 48 states at bonds up to 256 (512 rows): 51.0 us with the next
 // panel read back from memory, V read twice and the matrices' strips in
 // order, 44.7 now.
 __global__ __launch_bounds__(512, 1) void qrs_update_kernel(const QrArgs args, int p) {
